@@ -220,7 +220,11 @@ typedef struct {
                                       1, with the pols of a subband sharing their fringe
                                       phasors, no word prefetch and the fractional-delay
                                       phasors stepped at the store (bit-identical to 1).
-                                      2-4 and 8 apply to FP32 spectra only. */
+                                      2-4 and 8 apply to FP32 spectra only.  FP32
+                                      jobs, and FP16 ones of 1024 frames and more,
+                                      of FFT length up to 16384 whose fringe phase
+                                      is close enough to linear inside a frame run
+                                      the matrix-core F stage for 0-4 and 8. */
   int32_t xmac_frames_per_stage;   /* X-stage input staging: 8 = ring of 8 one-frame LDS
                                       stages filled by direct memory-to-LDS loads, products
                                       on the vector units (64-channel tiles, at most 32

@@ -29,11 +29,12 @@ HIPCC_FLAGS = [
 ]
 
 
-# Per-source additions.  k_xmac.hip: keep matrix-core accumulators in
+# Per-source additions.  k_xmac.hip, k_fmat.hip: keep matrix-core accumulators in
 # ordinary VGPRs (left to its heuristics the compiler splits them between
 # VGPRs and AGPRs and copies them back and forth inside the frame loop).
 FILE_FLAGS = {
     "k_xmac.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+    "k_fmat.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
 }
 
 

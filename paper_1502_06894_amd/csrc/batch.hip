@@ -292,7 +292,8 @@ int plan_fused(xc_ctx* c, const xc_job* jobs, int n, int lanes, FPlan& F) {
     F.L[j] = layout_of(&s, F.st[j].data(), P.tunes[j]);
     if (P.solo[j] || !fused_job_ok(s, jobs[j].st, P.tunes[j], P.layouts[j].T)) continue;
     const int N = 2 * s.n_chan;
-    const int W = fstage_fused_variant(N, s.n_pols, s.n_chan);
+    const int W =
+        fstage_fused_variant(N, fstage_matrix_ok(&s, jobs[j].st), s.n_pols, s.n_chan);
     auto key = std::make_pair(N, W);
     auto it = gidx.find(key);
     if (it == gidx.end()) {
@@ -370,7 +371,13 @@ int plan_fused(xc_ctx* c, const xc_job* jobs, int n, int lanes, FPlan& F) {
         it.fps = fps;
         it.slot_stride = L.slot_stride;
         it.task0 = R.ntasks;
-        R.ntasks += fstage_fused_tasks(g.N, g.W, s.n_stations, s.n_subbands * s.n_pols, it.nf);
+        if (g.W == kFstageMatrix) {
+          it.spt = fmat_subbands_per_task(g.N, s.n_stations, s.n_subbands, s.n_pols,
+                                          it.nf);
+          R.ntasks += fmat_tasks(g.N, s.n_stations, s.n_subbands, it.nf, it.spt);
+        } else {
+          R.ntasks += fstage_fused_tasks(g.N, g.W, s.n_stations, s.n_subbands * s.n_pols, it.nf);
+        }
         it.dblk0 = R.dblocks;
         R.dblocks += delays_fused_blocks(it.nf, s.n_stations, s.n_subbands);
         it.wblk0 = R.wblocks;

@@ -8,6 +8,7 @@
 
 #include "xc_fft.h"
 #include "xc_launch.h"
+#include "xc_spec.h"
 
 namespace xc {
 
@@ -43,44 +44,6 @@ struct FGeom {
 template <int N, int W>
 constexpr int fstage_twm() {
   return (W == 5 || W == kFstageLean) && N >= 512 ? kTwSplit : tw_default<N>();
-}
-
-// Spectrum element written by the F stage: FP32 complex, or for the MFMA X
-// path the power-of-two-scaled value as FP16 (Re, Im) or OCP e4m3 (Re, Im).
-// NT: non-temporal stores, for a wave that writes whole lines (consecutive
-// channels): a block's spectra (gigabytes) are read back by the X stage only
-// after the whole block is written, so keeping them in the caches would only
-// evict lines that are still useful (measured on MI355X: the X stage that
-// follows runs 9 % faster).  Scattered stores (every 16th channel, the
-// N = 32768 row kernel) stay ordinary so that the cache merges their lines.
-template <typename V>
-__device__ inline void store_spec(V* p, V v, bool nt) {
-  if (nt)
-    __builtin_nontemporal_store(v, p);
-  else
-    *p = v;
-}
-
-template <int OUT, bool NT = true>
-__device__ inline void put_spec(void* spec, size_t idx, float2 y, int e) {
-  if constexpr (OUT == kOutF32) {
-    typedef float f2 __attribute__((ext_vector_type(2)));
-    const f2 v = {y.x, y.y};
-    store_spec(static_cast<f2*>(spec) + idx, v, NT);
-  } else if constexpr (OUT == kOutF16) {
-    const float sx = ldexpf(y.x, e), sy = ldexpf(y.y, e);
-    typedef _Float16 h2 __attribute__((ext_vector_type(2)));
-    h2 h;
-    h.x = (_Float16)sx;
-    h.y = (_Float16)sy;
-    store_spec(static_cast<h2*>(spec) + idx, h, NT);
-  } else {
-    // the conversion maps overflow to NaN: saturate at the e4m3 maximum first
-    const float sx = fminf(fmaxf(ldexpf(y.x, e), -448.f), 448.f);
-    const float sy = fminf(fmaxf(ldexpf(y.y, e), -448.f), 448.f);
-    const int pk = __builtin_amdgcn_cvt_pk_fp8_f32(sx, sy, 0, false);
-    store_spec(static_cast<uint16_t*>(spec) + idx, (uint16_t)(pk & 0xffff), NT);
-  }
 }
 
 // Window words of one station-frame: the payload words holding samples
@@ -1041,8 +1004,8 @@ static hipError_t launch_fused_n(int waves, const FusedItem* items, int n_items,
   return hipErrorInvalidValue;
 }
 
-int fstage_fused_variant(int N, int n_pols, int n_chan) {
-  const int w = fstage_variant(0, n_pols, n_chan, kOutF32);
+int fstage_fused_variant(int N, bool mat, int n_pols, int n_chan) {
+  const int w = fstage_variant(0, mat, n_pols, n_chan, kOutF32, 0);
   // variant 2's fused form is kFstageShare (the same arithmetic)
   if (w == 2) return kFstageShare;
   return w == 0 && N >= kLeanMinN ? kFstageLean : w;
@@ -1061,6 +1024,7 @@ int fstage_fused_tasks(int N, int waves, int n_stations, int n_inputs, int nf) {
 
 hipError_t launch_fstage_fused(int N, int waves, const FusedItem* items, int n_items,
                                int n_tasks, const float2* tw, unsigned* ctr, hipStream_t s) {
+  if (waves == kFstageMatrix) return launch_fmat_fused(N, items, n_items, n_tasks, tw, s);
   switch (N) {
 #define XC_FFCASE(NN) \
   case NN: return launch_fused_n<NN>(waves, items, n_items, n_tasks, tw, ctr, s);
@@ -1079,10 +1043,13 @@ bool fstage_supported(int N) {
   }
 }
 
-hipError_t launch_fstage(int N, const DevJob* job, int n_stations, int n_inputs,
+hipError_t launch_fstage(int N, const DevJob* job, int n_stations, int n_subbands, int n_inputs,
                          const DelayRec* drec, const PhaseRec* prec, const float2* tw,
                          void* spec, const int8_t* scale_exp, int nf, int waves, int out,
                          unsigned* ctr, float2* scratch, hipStream_t s) {
+  if (waves == kFstageMatrix)
+    return launch_fmat(N, job, n_stations, n_subbands, n_inputs / n_subbands, drec, prec, tw, spec,
+                       scale_exp, nf, out, s);
   if (N == kBigN) {
     if (out == kOutF32) {
       if (!ctr) return hipErrorInvalidValue;

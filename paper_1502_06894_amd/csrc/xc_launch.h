@@ -28,6 +28,7 @@ struct FusedItem {
   int64_t f0;              // first frame of the block
   int32_t nf;              // frames in the block
   int32_t fps;             // X stage: frames per FP32 slice
+  int32_t spt;             // matrix-core F stage: subbands per task
   int32_t task0;           // F stage: tasks before this item
   int32_t dblk0;           // delay kernel: workgroups before this item
   int32_t wblk0;           // weight kernel: workgroups before this item
@@ -109,16 +110,33 @@ constexpr int kFstageShare = 8;
 constexpr int kShareMaxN = 4096;
 constexpr int kLeanMinN = 8192;
 constexpr int kLeanGroup = 4;   // inputs per lean task
-// The F-stage variant a job runs: the tuned one, else for FP32 spectra up to
+// kFstageMatrix: the first pass on the matrix cores (k_fmat.hip), for jobs that
+// pass fstage_matrix_ok.
+constexpr int kFstageMatrix = 9;
+constexpr int kMaxMatrixN = 16384;
+// The F-stage variant a job runs.  `mat` (the job passes fstage_matrix_ok, and
+// low-precision spectra matrix_out_ok): the matrix-core kernel, except where
+// variant 5 or 7 is tuned, which round their own way.
+// Otherwise the tuned one, else for FP32 spectra up to
 // N = kShareMaxN variant 2 for dual-pol jobs (pols share their fringe phasors,
 // with the word prefetch and held fractional-delay phasors) and lean tasks
 // for single-pol jobs from N = 1024; 0 otherwise (lean tasks from kLeanMinN).
 // Measured on MI355X, F stage of 10-station, 2-subband jobs against the
 // previous defaults: dual-pol N = 1024 / 2048 / 4096 -2 / -3 / -8 %,
 // single-pol N = 1024 / 2048 / 4096 -7 / -9 / -3 %.
-inline int fstage_variant(int tuned, int n_pols, int n_chan, int out) {
-  if (tuned != 0) return tuned;
+// Low-precision spectra: the kernels round differently in FP32, so a few
+// spectra land on the neighbouring FP16 or e4m3 value (2e-3 of the FP16 ones).
+// Over 1024 frames of FP16 that averages to below 5e-6 of the products; e4m3's
+// coarser steps would need some 16 000 and keep the vector kernel, as does
+// FP16 at 256 points, where its 16-channel runs leave the matrix kernel 3 % behind.
+inline bool matrix_out_ok(int N, int out, int64_t n_frames) {
+  return out == kOutF32 || (out == kOutF16 && N > 256 && n_frames >= 1024);
+}
+inline int fstage_variant(int tuned, bool mat, int n_pols, int n_chan, int out, int64_t n_frames) {
   const int N = 2 * n_chan;
+  if (mat && tuned != 5 && tuned != kFstageLean && matrix_out_ok(N, out, n_frames))
+    return kFstageMatrix;
+  if (tuned != 0) return tuned;
   if (out != kOutF32 || N > kShareMaxN) return 0;
   if (n_pols == 2) return 2;
   return N >= 1024 ? kFstageLean : 0;
@@ -127,10 +145,20 @@ constexpr int kMaxRateCorrectN = 16384;   // the drift correction runs in the on
 // ctr: task counter, zero at launch (launch_delays clears it), one per concurrent launch.
 // scratch: fstage_scratch_bytes(...) of device memory (N = 32768 with FP16 / e4m3 spectra
 // only; else unused).
-hipError_t launch_fstage(int N, const DevJob* job, int n_stations, int n_inputs,
+hipError_t launch_fstage(int N, const DevJob* job, int n_stations, int n_subbands, int n_inputs,
                          const DelayRec* drec, const PhaseRec* prec, const float2* tw,
                          void* spec, const int8_t* scale_exp, int nf, int waves, int out,
                          unsigned* ctr, float2* scratch, hipStream_t s);
+// The F stage on the matrix cores (N <= 16384, any output; the job must pass
+// fstage_matrix_ok): its tasks, each of spt subbands of a station and frame group.
+hipError_t launch_fmat(int N, const DevJob* job, int n_stations, int n_subbands, int n_pols,
+                       const DelayRec* drec, const PhaseRec* prec, const float2* tw, void* spec,
+                       const int8_t* scale_exp, int nf, int out, hipStream_t s);
+hipError_t launch_fmat_fused(int N, const FusedItem* items, int n_items, int n_tasks,
+                             const float2* tw, hipStream_t s);
+int fmat_subbands_per_task(int N, int n_stations, int n_subbands, int n_pols, int nf);
+int fmat_frames_per_task(int N);
+int fmat_tasks(int N, int n_stations, int n_subbands, int nf, int spt);
 // Scratch the F stage needs for nf frames (nonzero for N = 32768: its four-step
 // FFT goes through memory).
 size_t fstage_scratch_bytes(int N, int n_stations, int n_inputs, int nf, int out);
@@ -190,7 +218,7 @@ hipError_t launch_fstage_fused(int N, int waves, const FusedItem* items, int n_i
 // F-stage tasks of an item (job with S stations and n_inputs inputs, nf frames).
 int fstage_fused_tasks(int N, int waves, int n_stations, int n_inputs, int nf);
 // The F-stage variant of a fused batch item: what the per-job path would run.
-int fstage_fused_variant(int N, int n_pols, int n_chan);
+int fstage_fused_variant(int N, bool mat, int n_pols, int n_chan);
 // X stage over every item (all with inputs padded to Mp = MP, 64-channel tiles:
 // the matrix cores fed through the LDS ring); workgroups of one item:
 // xmac_fused_blocks.

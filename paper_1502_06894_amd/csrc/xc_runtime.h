@@ -139,6 +139,9 @@ int upload_desc(xc_ctx* c, const xc_setup* s, const xc_station* st, const Layout
 // `stream` before the finalise).
 // Does any station ask for the drift correction inside frames?
 bool any_rate_correct(const xc_setup* s, const xc_station* st);
+// Can the job's F stage run on the matrix cores (N <= 16384, and a fringe phase
+// whose curvature inside a frame is small enough for that kernel)?
+bool fstage_matrix_ok(const xc_setup* s, const xc_station* st);
 int enqueue_job(xc_ctx* c, const xc_setup* s, const xc_station* st, const xc_output* out,
                 const DevJob* dj, unsigned char* arena, const Layout& L, const xc_tuning& tu,
                 hipStream_t stream, hipStream_t xs = nullptr);

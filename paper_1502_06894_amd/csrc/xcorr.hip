@@ -160,6 +160,39 @@ bool any_rate_correct(const xc_setup* s, const xc_station* st) {
   return false;
 }
 
+bool fstage_matrix_ok(const xc_setup* s, const xc_station* st) {
+  const int N = 2 * s->n_chan;
+  if (N > kMaxMatrixN) return false;
+  // largest |phi2| (turns per squared sample) of the sub-integration: the
+  // second derivative's bound at the time furthest from the polynomial's origin
+  const double t0 = (double)s->sub_start / s->fs_hz;
+  const double t1 = (double)(s->sub_start + s->n_frames * (int64_t)N) / s->fs_hz;
+  const double t = fmax(fabs(t0), fabs(t1));
+  auto second = [&](const double* c, int deg) {
+    double a = 0.0;
+    for (int k = deg; k >= 2; --k) a = a * t + (double)(k * (k - 1)) * fabs(c[k]);
+    return a;
+  };
+  double lo = 0.0, phi2 = 0.0;
+  for (int b = 0; b < s->n_subbands; ++b) lo = fmax(lo, fabs(s->lo_hz[b]));
+  for (int b = 0; b < s->n_subbands; ++b)
+    if (!(fabs(s->lo_hz[b]) <= lo)) return false;   // not a number
+  for (int i = 0; i < s->n_stations; ++i) {
+    const xc_station& x = st[i];
+    for (int b = 0; b < (x.phase_poly ? s->n_subbands : 1); ++b) {
+      const double a = x.phase_poly ? second(x.phase_poly + b * (x.poly_deg + 1), x.poly_deg)
+                                    : lo * second(x.delay_poly, x.poly_deg);
+      if (!(a / (2.0 * s->fs_hz * s->fs_hz) <= phi2)) phi2 = a / (2.0 * s->fs_hz * s->fs_hz);
+      if (!(phi2 >= 0.0)) return false;
+    }
+  }
+  // left out of the phase, in turns: within a frame 2 phi2 (t - T/2) T (e - 8) <=
+  // N^2 phi2 / 32 and N^2 phi2 / 800 from the step of j; between the F frames
+  // of a task, which share their middle's slope, 9/16 (F - 1) N^2 phi2
+  const int F = fmat_frames_per_task(N);
+  return phi2 * (double)N * (double)N * (0.0325 + 0.5625 * (F - 1)) <= 3e-8;
+}
+
 Layout layout_of(const xc_setup* s, const xc_station* st, const xc_tuning& tu, bool overlap) {
   Layout L;
   const int S = s->n_stations, nsb = s->n_subbands, M = S * s->n_pols;
@@ -295,6 +328,7 @@ int enqueue_job(xc_ctx* c, const xc_setup* s, const xc_station* st, const xc_out
   void* spec = arena + L.spec;
   const bool overlap = L.nbuf == 2 && xs != nullptr;
   const bool rate_pass = any_rate_correct(s, st);
+  const bool mat = fstage_matrix_ok(s, st);
   double2* vacc = reinterpret_cast<double2*>(arena + L.vacc);
   double* wacc = reinterpret_cast<double*>(arena + L.wacc);
   int8_t* sexp = reinterpret_cast<int8_t*>(arena + L.sexp);
@@ -319,7 +353,7 @@ int enqueue_job(xc_ctx* c, const xc_setup* s, const xc_station* st, const xc_out
     e = launch_delays(dj, S, nsb, 0, L.n_scale, drec, prec, ctr0, stream);
     if (e == hipSuccess)
       e = timed(c, XC_K_FSTAGE, stream, [&] {
-        return launch_fstage(N, dj, S, nsb * s->n_pols, drec, prec, c->d_tw, spec, nullptr,
+        return launch_fstage(N, dj, S, nsb, nsb * s->n_pols, drec, prec, c->d_tw, spec, nullptr,
                              L.n_scale, 0, kOutF32, ctr0,
                              reinterpret_cast<float2*>(arena + L.scratch), stream);
       });
@@ -351,15 +385,16 @@ int enqueue_job(xc_ctx* c, const xc_setup* s, const xc_station* st, const xc_out
     });
     if (e != hipSuccess) return hip_fail(c, e, "delays");
     e = timed(c, XC_K_FSTAGE, stream, [&] {
-      return launch_fstage(N, dj, S, nsb * s->n_pols, drec_p, prec_p, c->d_tw, spec_p, sexp, nf,
-                           fstage_variant(tu.fstage_waves_per_simd, s->n_pols, s->n_chan, L.out),
+      return launch_fstage(N, dj, S, nsb, nsb * s->n_pols, drec_p, prec_p, c->d_tw, spec_p, sexp, nf,
+                           fstage_variant(tu.fstage_waves_per_simd, mat, s->n_pols, s->n_chan, L.out,
+                                         s->n_frames),
                            L.out, ctr_p,
                            reinterpret_cast<float2*>(arena + L.scratch), stream);
     });
     if (e != hipSuccess) return hip_fail(c, e, "fstage");
     if (rate_pass) {
       e = timed(c, XC_K_FSTAGE, stream, [&] {
-        return launch_fstage(N, dj, S, nsb * s->n_pols, drec_p, prec_p, c->d_tw, spec_p, sexp,
+        return launch_fstage(N, dj, S, nsb, nsb * s->n_pols, drec_p, prec_p, c->d_tw, spec_p, sexp,
                              nf, kFstageRatePass, L.out, ctr_p + 1,
                              reinterpret_cast<float2*>(arena + L.scratch), stream);
       });
@@ -796,14 +831,15 @@ int xc_debug_spectra(xc_ctx* c, const xc_setup* s, const xc_station* st, int64_t
   unsigned* ctr = reinterpret_cast<unsigned*>(p.arena + p.L.drec + p.L.ctr_off);
   hipError_t e = launch_delays(dj, s->n_stations, s->n_subbands, frame0, n, drec, prec, ctr, stream);
   if (e == hipSuccess)
-    e = launch_fstage(2 * s->n_chan, dj, s->n_stations, s->n_subbands * s->n_pols, drec, prec,
-                      c->d_tw, spectra, nullptr, n,
-                      fstage_variant(p.tu.fstage_waves_per_simd, s->n_pols, s->n_chan, kOutF32),
+    e = launch_fstage(2 * s->n_chan, dj, s->n_stations, s->n_subbands,
+                      s->n_subbands * s->n_pols, drec, prec, c->d_tw, spectra, nullptr, n,
+                      fstage_variant(p.tu.fstage_waves_per_simd, fstage_matrix_ok(s, st),
+                                     s->n_pols, s->n_chan, kOutF32, s->n_frames),
                       kOutF32, ctr,
                       reinterpret_cast<float2*>(p.arena + p.L.scratch), stream);
   if (e == hipSuccess && any_rate_correct(s, st))
-    e = launch_fstage(2 * s->n_chan, dj, s->n_stations, s->n_subbands * s->n_pols, drec, prec,
-                      c->d_tw, spectra, nullptr, n, kFstageRatePass, kOutF32, ctr + 1,
+    e = launch_fstage(2 * s->n_chan, dj, s->n_stations, s->n_subbands,
+                      s->n_subbands * s->n_pols, drec, prec, c->d_tw, spectra, nullptr, n, kFstageRatePass, kOutF32, ctr + 1,
                       reinterpret_cast<float2*>(p.arena + p.L.scratch), stream);
   return e == hipSuccess ? XC_OK : hip_fail(c, e, "debug_spectra");
 }
