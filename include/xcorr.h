@@ -268,8 +268,8 @@ int xc_get_tuning(const xc_ctx* ctx, xc_tuning* t);
  * every job of the group and runs all of them as one delay launch, one
  * F-stage launch that is persistent over the tasks of every job's block, and
  * one X-stage launch per input-tile shape.  Groups of different FFT lengths run side by side on
- * n_lanes concurrent HIP streams ("lanes"); one ingest (each distinct
- * recording once), one clear of all accumulators and one finalise serve the
+ * n_lanes concurrent HIP streams ("lanes"); one clear of the jobs'
+ * weights and one finalise serve the
  * whole batch.  Long jobs (their own launches fill the GPU) and jobs the
  * fused kernels do not take (FP16 / FP8 precision, 16384 channels, drift
  * correction, or an X-stage tuning other than the default or the rings) run as

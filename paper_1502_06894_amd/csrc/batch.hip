@@ -154,7 +154,7 @@ int upload_batch_desc(xc_ctx* c, const xc_job* jobs, int n, const Plan& P, unsig
   if (e != hipSuccess) return hip_fail(c, e, "batch descriptors");
   for (int j = 0; j < n; ++j)
     build_desc(&P.setups[j], jobs[j].st, P.layouts[j], ws + P.desc_off[j],
-               ws + P.arena_off[P.lane_of[j]], c->h_batch + P.desc_off[j]);
+               c->h_batch + P.desc_off[j]);
   e = hipMemcpyAsync(ws, c->h_batch, P.desc_bytes, hipMemcpyHostToDevice, stream);
   if (e == hipSuccess) e = hipEventRecord(c->batch_ev, stream);
   return e == hipSuccess ? XC_OK : hip_fail(c, e, "batch descriptor upload");
@@ -170,7 +170,7 @@ int enqueue_batch(xc_ctx* c, const xc_job* jobs, const Plan& P, unsigned char* w
     for (int j : P.order[l]) {
       const DevJob* dj = reinterpret_cast<const DevJob*>(ws + P.desc_off[j]);
       int rc = enqueue_job(c, &P.setups[j], jobs[j].st, &jobs[j].out, dj, ws + P.arena_off[l],
-                           P.layouts[j], P.tunes[j], c->lanes[l]);
+                           P.layouts[j], P.tunes[j], false, c->lanes[l]);
       if (rc != XC_OK) {
         c->last_error = "job " + std::to_string(j) + ": " + c->last_error;
         return rc;
@@ -187,14 +187,14 @@ int enqueue_batch(xc_ctx* c, const xc_job* jobs, const Plan& P, unsigned char* w
 // Short jobs (at most kFusedMaxBlocks blocks) of one FFT length (and F-stage
 // variant) form a group.  A group runs in rounds: round r takes block r of
 // every job of the group that has one, and
-// runs it as one delay, one weight, one F-stage launch (persistent over the
+// runs it as one delay, one F-stage launch (persistent over the
 // tasks of all those blocks) and one X-stage launch per input-tile shape.  A
 // job never has two blocks in one round, so every accumulator slot still has
 // one writer per launch and a job's blocks add in block order: results are
 // bit-identical to the job run alone with the same block size.  Groups run on
 // lanes side by side with the long jobs and those the fused kernels do not
-// take, which run as single jobs on the lanes.  One ingest (each distinct recording once), one clear of all
-// accumulators and one finalise serve the whole batch.
+// take, which run as single jobs on the lanes.  One clear of all weights and one
+// finalise serve the whole batch.
 
 struct XClass {
   int Mp, first, n, blocks;        // items [first, first + n) of the round, X workgroups
@@ -202,7 +202,7 @@ struct XClass {
 
 struct FRound {
   int first = 0, n = 0;            // items in the batch's item table
-  int dblocks = 0, wblocks = 0, ntasks = 0;
+  int dblocks = 0, ntasks = 0;
   std::vector<XClass> xc;
 };
 
@@ -217,7 +217,6 @@ struct FGroup {
 struct FPlan {
   Plan P;                                   // setups (batch block sizes), tunings, descriptors
   std::vector<Layout> L;                    // per job: layout used by this executor
-  std::vector<std::vector<xc_station>> st;  // per job: stations, frame_ok pointing at masks
   std::vector<int> group_of;                // per job: fused group, or -1 (single job)
   std::vector<FGroup> groups;
   std::vector<std::vector<int>> lane_groups, lane_jobs;
@@ -225,13 +224,10 @@ struct FPlan {
   std::vector<int> item_job;                // job of each item
   std::vector<FusedOut> outs;
   std::vector<int> out_job;
-  std::vector<FusedMask> masks;
-  std::vector<size_t> mask_off;             // per mask: offset of its bytes
-  std::vector<std::vector<int>> st_mask;    // per job, station: mask index or -1 (caller's)
-  size_t items_off = 0, outs_off = 0, masks_off = 0, blob_bytes = 0;
-  size_t maskbytes_off = 0, acc_off = 0, acc_bytes = 0, ctr_off = 0;
-  std::vector<size_t> vacc_off, wacc_off, blk_off, arena_off;
-  int fin_blocks = 0, ingest_blocks = 0;
+  size_t items_off = 0, outs_off = 0, blob_bytes = 0;
+  size_t wst_off = 0, wst_bytes = 0, ctr_off = 0;   // every fused job's weights
+  std::vector<size_t> vacc_off, wst_job_off, blk_off, arena_off;
+  int fin_blocks = 0;
   size_t total = 0;
 };
 
@@ -254,42 +250,12 @@ int plan_fused(xc_ctx* c, const xc_job* jobs, int n, int lanes, FPlan& F) {
   if (rc != XC_OK) return rc;
   const Plan& P = F.P;
   F.L.resize(n);
-  F.st.resize(n);
   F.group_of.assign(n, -1);
-  F.st_mask.resize(n);
-  // distinct recordings without a caller mask: one mask each
-  std::map<std::pair<const void*, int64_t>, int> mask_idx;
-  size_t mbytes = 0;
-  for (int j = 0; j < n; ++j) {
-    const xc_setup& s = P.setups[j];
-    F.st[j].assign(jobs[j].st, jobs[j].st + s.n_stations);
-    F.st_mask[j].assign(s.n_stations, -1);
-    if (P.solo[j] || !fused_job_ok(s, jobs[j].st, P.tunes[j], P.layouts[j].T)) continue;
-    for (int i = 0; i < s.n_stations; ++i) {
-      const xc_station& x = jobs[j].st[i];
-      if (x.frame_ok) continue;
-      auto key = std::make_pair(x.frames, x.n_frames_m5b);
-      auto it = mask_idx.find(key);
-      if (it == mask_idx.end()) {
-        it = mask_idx.emplace(key, (int)F.masks.size()).first;
-        FusedMask m{};
-        m.words = static_cast<const uint32_t*>(x.frames);
-        m.n_frames = x.n_frames_m5b;
-        m.blk0 = F.ingest_blocks;
-        F.ingest_blocks += ingest_fused_blocks(x.n_frames_m5b);
-        F.masks.push_back(m);
-        F.mask_off.push_back(mbytes);
-        mbytes += align_up((size_t)x.n_frames_m5b);
-      }
-      F.st_mask[j][i] = it->second;
-      F.st[j][i].frame_ok = reinterpret_cast<const uint8_t*>(1);   // sized as caller-supplied
-    }
-  }
   // groups by (FFT length, F-stage variant)
   std::map<std::pair<int, int>, int> gidx;
   for (int j = 0; j < n; ++j) {
     const xc_setup& s = P.setups[j];
-    F.L[j] = layout_of(&s, F.st[j].data(), P.tunes[j]);
+    F.L[j] = layout_of(&s, jobs[j].st, P.tunes[j]);
     if (P.solo[j] || !fused_job_ok(s, jobs[j].st, P.tunes[j], P.layouts[j].T)) continue;
     const int N = 2 * s.n_chan;
     const int W =
@@ -343,9 +309,10 @@ int plan_fused(xc_ctx* c, const xc_job* jobs, int n, int lanes, FPlan& F) {
     for (size_t g = 0; g < F.groups.size(); ++g)
       for (int j : F.groups[g].jobs) F.group_of[j] = (int)g;
   }
-  // workspace: [descriptors][tables][masks][accumulators][counters][blocks][single-job arenas]
+  // workspace: [descriptors][tables][weights][accumulators][counters][blocks][single-job arenas]
   size_t off = align_up(P.desc_bytes);
   // rounds and items (tables are laid out once the item count is known)
+  std::vector<int> slots(n, 0);   // accumulator slots a job's rounds so far have written
   for (FGroup& g : F.groups) {
     // items of a round ordered by padded input count, so that each X launch
     // takes a contiguous run of them
@@ -369,6 +336,8 @@ int plan_fused(xc_ctx* c, const xc_job* jobs, int n, int lanes, FPlan& F) {
         int n_splits = 0, fps = 0;
         xmac_splits(it.nf, L.fps, M, s.n_chan, s.n_subbands, n_splits, fps);
         it.fps = fps;
+        it.n_init = slots[j];
+        slots[j] = std::max(slots[j], slots_used(it.nf, L.fps, M, s.n_chan, s.n_subbands));
         it.slot_stride = L.slot_stride;
         it.task0 = R.ntasks;
         if (g.W == kFstageMatrix) {
@@ -379,9 +348,7 @@ int plan_fused(xc_ctx* c, const xc_job* jobs, int n, int lanes, FPlan& F) {
           R.ntasks += fstage_fused_tasks(g.N, g.W, s.n_stations, s.n_subbands * s.n_pols, it.nf);
         }
         it.dblk0 = R.dblocks;
-        R.dblocks += delays_fused_blocks(it.nf, s.n_stations, s.n_subbands);
-        it.wblk0 = R.wblocks;
-        R.wblocks += weights_fused_blocks(it.nf, s.n_stations);
+        R.dblocks += delays_fused_blocks(it.nf, s.n_subbands);
         const int Mp = (M + 3) / 4 * 4;
         if (R.xc.empty() || R.xc.back().Mp != Mp)
           R.xc.push_back({Mp, (int)F.items.size() - R.first, 0, 0});
@@ -401,7 +368,7 @@ int plan_fused(xc_ctx* c, const xc_job* jobs, int n, int lanes, FPlan& F) {
     if (F.group_of[j] < 0) continue;
     const xc_setup& s = P.setups[j];
     FusedOut o{};
-    o.n_slots = F.L[j].n_slots;
+    o.n_slots = slots[j];
     o.slot_stride = F.L[j].slot_stride;
     o.S = s.n_stations;
     o.P = s.n_pols;
@@ -418,22 +385,21 @@ int plan_fused(xc_ctx* c, const xc_job* jobs, int n, int lanes, FPlan& F) {
   off += align_up(F.items.size() * sizeof(FusedItem));
   F.outs_off = off;
   off += align_up(F.outs.size() * sizeof(FusedOut));
-  F.masks_off = off;
-  off += align_up(F.masks.size() * sizeof(FusedMask));
   F.blob_bytes = off;
-  F.maskbytes_off = off;
-  off += mbytes;
-  F.acc_off = off;
+  F.wst_off = off;
+  F.wst_job_off.assign(n, 0);
+  for (int j = 0; j < n; ++j) {
+    if (F.group_of[j] < 0) continue;
+    F.wst_job_off[j] = off;
+    off += F.L[j].wst_bytes;
+  }
+  F.wst_bytes = off - F.wst_off;
   F.vacc_off.assign(n, 0);
-  F.wacc_off.assign(n, 0);
   for (int j = 0; j < n; ++j) {
     if (F.group_of[j] < 0) continue;
     F.vacc_off[j] = off;
-    off += (size_t)F.L[j].n_slots * F.L[j].slot_stride * sizeof(double2);
-    F.wacc_off[j] = off;
-    off += align_up((size_t)P.setups[j].n_stations * P.setups[j].n_stations * sizeof(double));
+    off += align_up((size_t)F.L[j].n_slots * F.L[j].slot_stride * sizeof(double2));
   }
-  F.acc_bytes = off - F.acc_off;
   for (FGroup& g : F.groups) {
     g.ctr_off = off;
     off += kAlign;
@@ -477,7 +443,6 @@ int plan_fused(xc_ctx* c, const xc_job* jobs, int n, int lanes, FPlan& F) {
   std::vector<size_t> lane_arena(lanes, 0);
   for (int j = 0; j < n; ++j) {
     if (F.group_of[j] >= 0) continue;
-    F.L[j] = layout_of(&P.setups[j], jobs[j].st, P.tunes[j]);   // its own masks
     lane_arena[lane_of_job[j]] = std::max(lane_arena[lane_of_job[j]], align_up(F.L[j].total));
   }
   std::vector<size_t> lane_off(lanes, 0);
@@ -497,10 +462,6 @@ int plan_fused(xc_ctx* c, const xc_job* jobs, int n, int lanes, FPlan& F) {
 int fill_and_upload_fused(xc_ctx* c, const xc_job* jobs, int n, FPlan& F, unsigned char* ws,
                           hipStream_t stream) {
   const Plan& P = F.P;
-  for (size_t m = 0; m < F.masks.size(); ++m) F.masks[m].ok = ws + F.maskbytes_off + F.mask_off[m];
-  for (int j = 0; j < n; ++j)
-    for (size_t i = 0; i < F.st_mask[j].size(); ++i)
-      if (F.st_mask[j][i] >= 0) F.st[j][i].frame_ok = F.masks[F.st_mask[j][i]].ok;
   for (size_t k = 0; k < F.items.size(); ++k) {
     const int j = F.item_job[k];
     const Layout& L = F.L[j];
@@ -511,13 +472,13 @@ int fill_and_upload_fused(xc_ctx* c, const xc_job* jobs, int n, FPlan& F, unsign
     it.prec = reinterpret_cast<PhaseRec*>(b + L.drec_bytes);
     it.spec = reinterpret_cast<float2*>(b + L.drec_bytes + L.prec_bytes);
     it.vacc = reinterpret_cast<double2*>(ws + F.vacc_off[j]);
-    it.wst = reinterpret_cast<double*>(ws + F.wacc_off[j]);
+    it.wst = reinterpret_cast<unsigned long long*>(ws + F.wst_job_off[j]);
   }
   for (size_t k = 0; k < F.outs.size(); ++k) {
     const int j = F.out_job[k];
     FusedOut& o = F.outs[k];
     o.vacc = reinterpret_cast<const double2*>(ws + F.vacc_off[j]);
-    o.wst = reinterpret_cast<const double*>(ws + F.wacc_off[j]);
+    o.wst = reinterpret_cast<const unsigned long long*>(ws + F.wst_job_off[j]);
     o.vis = static_cast<float2*>(jobs[j].out.vis);
     o.weight = jobs[j].out.weight;
   }
@@ -533,17 +494,12 @@ int fill_and_upload_fused(xc_ctx* c, const xc_job* jobs, int n, FPlan& F, unsign
   }
   if (e != hipSuccess) return hip_fail(c, e, "batch descriptors");
   memset(c->h_batch, 0, F.blob_bytes);
-  for (int j = 0; j < n; ++j) {
-    // single jobs keep their own masks in their own arena
-    const bool fused = F.group_of[j] >= 0;
-    build_desc(&P.setups[j], fused ? F.st[j].data() : jobs[j].st, F.L[j], ws + P.desc_off[j],
-               fused ? nullptr : ws + F.arena_off[j], c->h_batch + P.desc_off[j]);
-  }
+  for (int j = 0; j < n; ++j)
+    build_desc(&P.setups[j], jobs[j].st, F.L[j], ws + P.desc_off[j], c->h_batch + P.desc_off[j]);
   for (size_t k = 0; k < F.items.size(); ++k)
     F.items[k].jd = *reinterpret_cast<const DevJob*>(c->h_batch + P.desc_off[F.item_job[k]]);
   memcpy(c->h_batch + F.items_off, F.items.data(), F.items.size() * sizeof(FusedItem));
   memcpy(c->h_batch + F.outs_off, F.outs.data(), F.outs.size() * sizeof(FusedOut));
-  memcpy(c->h_batch + F.masks_off, F.masks.data(), F.masks.size() * sizeof(FusedMask));
   e = hipMemcpyAsync(ws, c->h_batch, F.blob_bytes, hipMemcpyHostToDevice, stream);
   if (e == hipSuccess) e = hipEventRecord(c->batch_ev, stream);
   return e == hipSuccess ? XC_OK : hip_fail(c, e, "batch descriptor upload");
@@ -555,8 +511,7 @@ int enqueue_group(xc_ctx* c, const FPlan& F, const FGroup& g, unsigned char* ws,
   for (const FRound& R : g.rounds) {
     const FusedItem* it = items + R.first;
     hipError_t e = timed(c, XC_K_DELAYS, s, [&] {
-      hipError_t r = launch_delays_fused(it, R.n, R.dblocks, ctr, s);
-      return r == hipSuccess ? launch_weights_fused(it, R.n, R.wblocks, s) : r;
+      return launch_delays_fused(it, R.n, R.dblocks, ctr, s);
     });
     if (e != hipSuccess) return hip_fail(c, e, "fused delays");
     e = timed(c, XC_K_FSTAGE, s, [&] {
@@ -576,15 +531,10 @@ int enqueue_fused(xc_ctx* c, const xc_job* jobs, const FPlan& F, unsigned char* 
                   hipStream_t origin) {
   const int n = (int)F.P.setups.size();
   hipError_t e = hipSuccess;
-  if (!F.masks.empty())
-    e = timed(c, XC_K_INGEST, origin, [&] {
-      return launch_ingest_fused(reinterpret_cast<const FusedMask*>(ws + F.masks_off),
-                                 (int)F.masks.size(), F.ingest_blocks, origin);
-    });
-  if (e == hipSuccess && F.acc_bytes)
+  if (F.wst_bytes)
     e = timed(c, XC_K_ZERO, origin, [&] {
-      return launch_zero(reinterpret_cast<double*>(ws + F.acc_off), F.acc_bytes / sizeof(double),
-                         origin);
+      return launch_zero(reinterpret_cast<unsigned long long*>(ws + F.wst_off),
+                         F.wst_bytes / sizeof(unsigned long long), origin);
     });
   if (e != hipSuccess) return hip_fail(c, e, "fused prologue");
   e = hipEventRecord(c->fork_ev, origin);
@@ -598,7 +548,7 @@ int enqueue_fused(xc_ctx* c, const xc_job* jobs, const FPlan& F, unsigned char* 
     for (int j : F.lane_jobs[l]) {
       const DevJob* dj = reinterpret_cast<const DevJob*>(ws + F.P.desc_off[j]);
       const int rc = enqueue_job(c, &F.P.setups[j], jobs[j].st, &jobs[j].out, dj,
-                                 ws + F.arena_off[j], F.L[j], F.P.tunes[j], c->lanes[l]);
+                                 ws + F.arena_off[j], F.L[j], F.P.tunes[j], false, c->lanes[l]);
       if (rc != XC_OK) {
         c->last_error = "job " + std::to_string(j) + ": " + c->last_error;
         return rc;
@@ -760,10 +710,11 @@ int xc_autotune(xc_ctx* c, const xc_setup* setup, const xc_station* st, const xc
     if (align_up(L.desc_bytes) + L.total > ws_bytes) continue;
     unsigned char* desc = static_cast<unsigned char*>(workspace);
     unsigned char* arena = desc + align_up(L.desc_bytes);
-    rc = upload_desc(c, &s, st, L, desc, arena, stream);
+    rc = upload_desc(c, &s, st, L, desc, stream);
     for (int rep = 0; rep < 3 && rc == XC_OK; ++rep) {
       if (rep == 1) e = hipEventRecord(a, stream);
-      rc = enqueue_job(c, &s, st, out, reinterpret_cast<const DevJob*>(desc), arena, L, tu, stream);
+      rc = enqueue_job(c, &s, st, out, reinterpret_cast<const DevJob*>(desc), arena, L, tu, false,
+                       stream);
     }
     if (rc != XC_OK) break;
     e = hipEventRecord(b, stream);

@@ -1,5 +1,5 @@
-// Small kernels: recording ingest (A0), delay/phase model per frame (A1),
-// accumulator clearing, finalise (A8) and the unpack test tap.
+// Small kernels: recording ingest (A0), delay/phase model per frame and
+// station-pair weights (A1), weight clearing, finalise (A8) and the unpack test tap.
 #include "xc_launch.h"
 
 namespace xc {
@@ -19,13 +19,13 @@ hipError_t launch_ingest(const uint32_t* words, int64_t n_frames, uint8_t* frame
   return hipGetLastError();
 }
 
-__global__ void k_zero(double* __restrict__ p, size_t n) {
+__global__ void k_zero(unsigned long long* __restrict__ p, size_t n) {
   for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
        i += (size_t)gridDim.x * blockDim.x)
-    p[i] = 0.0;
+    p[i] = 0;
 }
 
-hipError_t launch_zero(double* p, size_t n, hipStream_t s) {
+hipError_t launch_zero(unsigned long long* p, size_t n, hipStream_t s) {
   if (n == 0) return hipSuccess;
   size_t g = (n + 255) / 256;
   if (g > 65536) g = 65536;
@@ -34,8 +34,9 @@ hipError_t launch_zero(double* p, size_t n, hipStream_t s) {
 }
 
 // Delay record (subband 0 only) and phase record of frame fl of a block
-// starting at frame f0, station s, subband sb.
-__device__ inline void delay_phase_records(const DevJob& J, int s, int sb, int64_t f0, int fl,
+// starting at frame f0, station s, subband sb; the frame's validity for
+// subband 0.
+__device__ inline bool delay_phase_records(const DevJob& J, int s, int sb, int64_t f0, int fl,
                                            int nf, DelayRec* __restrict__ drec,
                                            PhaseRec* __restrict__ prec) {
   const DevStation& S = J.st[s];
@@ -45,150 +46,123 @@ __device__ inline void delay_phase_records(const DevJob& J, int s, int sb, int64
   // one thread per (frame, station, subband): each writes its subband's phase
   // record, the subband-0 thread also the frame's delay record
   prec[((size_t)s * J.n_subbands + sb) * nf + fl] = frame_phase(S, J, sb, t);
-  if (sb != 0) return;
+  if (sb != 0) return false;
   DelayRec r;
   frame_delay(S, J, f, &r.n_int, &r.d);
   r.base = J.sub_start + f * (int64_t)J.N + r.n_int - S.first_sample;
   const int64_t n_samples = S.n_frames_m5b * (int64_t)J.spf;
   bool ok = r.base >= 0 && r.base + J.N <= n_samples;
   if (ok) {
+    // the recording frames of the window: the caller's mask, else their sync
+    // words (four loads at a time)
     const int64_t a = r.base / J.spf, b = (r.base + J.N - 1) / J.spf;
-    for (int64_t m = a; m <= b; ++m) ok = ok && S.frame_ok[m] != 0;
+    int bad = 0;
+    if (S.frame_ok) {
+      for (int64_t m = a; m <= b; ++m) bad |= S.frame_ok[m] == 0;
+    } else {
+      for (int64_t m = a; m <= b; m += 4) {
+        uint32_t w[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) w[i] = S.words[(m + i < b ? m + i : b) * kFrameWords];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) bad |= w[i] != kSync;
+      }
+    }
+    ok = bad == 0;
   }
   r.valid = ok ? 1 : 0;
   double d1, d2;
   poly_derivs(S.delay_poly, S.poly_deg, t, d1, d2);
   r.rate = (float)d1;
   drec[(size_t)s * nf + fl] = r;
+  return ok;
 }
 
-// One thread per (station, block frame, subband).  Writes the subband's fringe
-// phase terms; the subband-0 thread also the integer/fractional delay, the
-// validity and the delay rate of the frame.
-__global__ void k_delays(const DevJob* __restrict__ job, int64_t f0, int nf,
-                         DelayRec* __restrict__ drec, PhaseRec* __restrict__ prec,
-                         unsigned* __restrict__ ctr) {
-  const int fl = blockIdx.x * blockDim.x + threadIdx.x;
-  const int s = blockIdx.y, sb = blockIdx.z;
-  if (ctr && fl == 0 && s == 0 && sb == 0) {
+// One workgroup: the frames of a 64-frame chunk (one a lane) of every station
+// (a wave each) for one subband.  For subband 0 the stations' validity masks
+// then meet in LDS and each station pair's count of common valid frames is
+// added to its total (wst, integers: exact in any order), so that no second
+// launch reads the records back.
+constexpr int kDelayFrames = 64;
+constexpr int kDelayWaves = 16;         // at most, in one workgroup
+
+__device__ __forceinline__ void delays_chunk(const DevJob& J, int64_t f0, int chunk, int sb, int nf,
+                                             DelayRec* __restrict__ drec,
+                                             PhaseRec* __restrict__ prec,
+                                             unsigned long long* __restrict__ wst) {
+  __shared__ unsigned long long mask[kMaxStations];
+  const int S = J.n_stations;
+  const int lane = threadIdx.x & 63, waves = blockDim.x >> 6;
+  const int fl = chunk * kDelayFrames + lane;
+  for (int s = threadIdx.x >> 6; s < S; s += waves) {
+    const bool ok = fl < nf && delay_phase_records(J, s, sb, f0, fl, nf, drec, prec);
+    const unsigned long long m = __ballot(ok);
+    if (lane == 0) mask[s] = m;
+  }
+  if (sb != 0 || !wst) return;
+  __syncthreads();
+  for (int p = threadIdx.x; p < S * S; p += blockDim.x) {
+    const int i = p / S, j = p - i * S;
+    if (j < i) continue;
+    const int n = __popcll(mask[i] & mask[j]);
+    if (n) atomicAdd(&wst[p], (unsigned long long)n);
+  }
+}
+
+__global__ void __launch_bounds__(64 * kDelayWaves)
+    k_delays(const DevJob* __restrict__ job, int64_t f0, int nf, DelayRec* __restrict__ drec,
+             PhaseRec* __restrict__ prec, unsigned* __restrict__ ctr,
+             unsigned long long* __restrict__ wst) {
+  if (ctr && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
     ctr[0] = 0u;   // the F stage's task counter
     ctr[1] = 0u;   // the drift-correction pass's
   }
-  if (fl >= nf) return;
-  delay_phase_records(*job, s, sb, f0, fl, nf, drec, prec);
+  delays_chunk(*job, f0, blockIdx.x, blockIdx.y, nf, drec, prec, wst);
 }
 
 hipError_t launch_delays(const DevJob* job, int n_stations, int n_subbands, int64_t f0, int nf,
-                         DelayRec* drec, PhaseRec* prec, unsigned* ctr, hipStream_t s) {
-  const int b = 64;
-  dim3 grid((nf + b - 1) / b, n_stations, n_subbands);
-  hipLaunchKernelGGL(k_delays, grid, dim3(b), 0, s, job, f0, nf, drec, prec, ctr);
+                         DelayRec* drec, PhaseRec* prec, unsigned* ctr, unsigned long long* wst,
+                         hipStream_t s) {
+  const dim3 grid((nf + kDelayFrames - 1) / kDelayFrames, n_subbands);
+  const int waves = n_stations < kDelayWaves ? n_stations : kDelayWaves;
+  hipLaunchKernelGGL(k_delays, grid, dim3(64 * waves), 0, s, job, f0, nf, drec, prec, ctr, wst);
   return hipGetLastError();
 }
 
-constexpr int kDelayThreads = 64;
+constexpr int kDelayFusedThreads = 256;
 
-int delays_fused_blocks(int nf, int n_stations, int n_subbands) {
-  return (nf + kDelayThreads - 1) / kDelayThreads * n_stations * n_subbands;
+int delays_fused_blocks(int nf, int n_subbands) {
+  return (nf + kDelayFrames - 1) / kDelayFrames * n_subbands;
 }
 
 // k_delays over the blocks of a fused round: workgroup -> (item, frame chunk,
-// station, subband).
-__global__ void __launch_bounds__(kDelayThreads)
+// subband).
+__global__ void __launch_bounds__(kDelayFusedThreads)
     k_delays_fused(const FusedItem* __restrict__ items, int n_items, unsigned* __restrict__ ctr) {
   const int it = fused_find(items, n_items, (int)blockIdx.x,
                             [](const FusedItem& I) { return I.dblk0; });
   const FusedItem& I = items[it];
-  const DevJob& J = I.jd;
   if (ctr && blockIdx.x == 0 && threadIdx.x == 0) {
     ctr[0] = 0u;
     ctr[1] = 0u;
   }
-  const int nfb = (I.nf + kDelayThreads - 1) / kDelayThreads;
-  int local = (int)blockIdx.x - I.dblk0;
-  const int fb = local % nfb;
-  local /= nfb;
-  const int s = local % J.n_stations, sb = local / J.n_stations;
-  const int fl = fb * kDelayThreads + (int)threadIdx.x;
-  if (fl >= I.nf) return;
-  delay_phase_records(J, s, sb, I.f0, fl, I.nf, I.drec, I.prec);
+  const int nfb = (I.nf + kDelayFrames - 1) / kDelayFrames;
+  const int local = (int)blockIdx.x - I.dblk0;
+  delays_chunk(I.jd, I.f0, local % nfb, local / nfb, I.nf, I.drec, I.prec, I.wst);
 }
 
 hipError_t launch_delays_fused(const FusedItem* items, int n_items, int n_blocks, unsigned* ctr,
                                hipStream_t s) {
   if (n_blocks <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_delays_fused, dim3(n_blocks), dim3(kDelayThreads), 0, s, items, n_items,
-                     ctr);
-  return hipGetLastError();
-}
-
-// One workgroup per station pair (si <= sj) and chunk of kWeightChunk frames:
-// count the frames valid for both and add the count to the pair's total.  The
-// counts are integers, exact in FP64 whatever order the chunks add in.
-constexpr int kWeightChunk = 2048;
-
-__device__ inline void pair_weights(const DelayRec* __restrict__ drec, int S, int nf,
-                                    double* __restrict__ wst, int si, int sj, int chunk,
-                                    int* part) {
-  const int f0 = chunk * kWeightChunk;
-  const int f1 = nf < f0 + kWeightChunk ? nf : f0 + kWeightChunk;
-  int cnt = 0;
-#pragma unroll 8
-  for (int f = f0 + (int)threadIdx.x; f < f1; f += blockDim.x)
-    cnt += drec[(size_t)si * nf + f].valid & drec[(size_t)sj * nf + f].valid;
-  part[threadIdx.x] = cnt;
-  __syncthreads();
-  for (int w = blockDim.x / 2; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) part[threadIdx.x] += part[threadIdx.x + w];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0 && part[0] != 0) atomicAdd(&wst[si * S + sj], (double)part[0]);
-}
-
-__global__ void k_weights(const DelayRec* __restrict__ drec, int S, int nf,
-                          double* __restrict__ wst) {
-  const int si = blockIdx.x, sj = blockIdx.y;
-  if (sj < si) return;
-  __shared__ int part[256];
-  pair_weights(drec, S, nf, wst, si, sj, blockIdx.z, part);
-}
-
-int weights_fused_blocks(int nf, int n_stations) {
-  return n_stations * n_stations * ((nf + kWeightChunk - 1) / kWeightChunk);
-}
-
-// k_weights over the blocks of a fused round: workgroup -> (item, si, sj, chunk).
-__global__ void k_weights_fused(const FusedItem* __restrict__ items, int n_items) {
-  const int it = fused_find(items, n_items, (int)blockIdx.x,
-                            [](const FusedItem& I) { return I.wblk0; });
-  const FusedItem& I = items[it];
-  const int S = I.jd.n_stations;
-  int local = (int)blockIdx.x - I.wblk0;
-  const int si = local % S;
-  local /= S;
-  const int sj = local % S, chunk = local / S;
-  if (sj < si) return;
-  __shared__ int part[256];
-  pair_weights(I.drec, S, I.nf, I.wst, si, sj, chunk, part);
-}
-
-hipError_t launch_weights_fused(const FusedItem* items, int n_items, int n_blocks, hipStream_t s) {
-  if (n_blocks <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_weights_fused, dim3(n_blocks), dim3(256), 0, s, items, n_items);
-  return hipGetLastError();
-}
-
-hipError_t launch_weights(const DelayRec* drec, int n_stations, int nf, double* wst,
-                          hipStream_t s) {
-  const dim3 grid(n_stations, n_stations, (nf + kWeightChunk - 1) / kWeightChunk);
-  hipLaunchKernelGGL(k_weights, grid, dim3(256), 0, s, drec, n_stations, nf, wst);
+  hipLaunchKernelGGL(k_delays_fused, dim3(n_blocks), dim3(kDelayFusedThreads), 0, s, items,
+                     n_items, ctr);
   return hipGetLastError();
 }
 
 // Element e of a job's output: the sum of its n_slots FP64 slots over the
 // weight of its station pair (W = 0 -> 0); the k = 0 element also writes W.
 __device__ inline void finalise_elem(const double2* __restrict__ vacc, int n_slots,
-                                     size_t slot_stride, const double* __restrict__ wst, int S,
+                                     size_t slot_stride, const unsigned long long* __restrict__ wst, int S,
                                      int P, int M, float2* __restrict__ vis,
                                      float* __restrict__ weight, int nbl, int n_chan, size_t e) {
   const size_t row = e / n_chan;          // sb * nbl + bl
@@ -200,7 +174,7 @@ __device__ inline void finalise_elem(const double2* __restrict__ vacc, int n_slo
     ++i;
   }
   const int j = i + rem;
-  const double w = wst[(i / P) * S + (j / P)];
+  const double w = (double)wst[(i / P) * S + (j / P)];
   double2 a = vacc[e];
   // fixed slot order; the loads of eight slots are issued together (a job of
   // few channels and baselines can have over a hundred slots)
@@ -225,7 +199,7 @@ __device__ inline void finalise_elem(const double2* __restrict__ vacc, int n_slo
 }
 
 __global__ void k_finalise(const double2* __restrict__ vacc, int n_slots, size_t slot_stride,
-                           const double* __restrict__ wst, int S, int P, int M,
+                           const unsigned long long* __restrict__ wst, int S, int P, int M,
                            float2* __restrict__ vis, float* __restrict__ weight, int nbl,
                            int n_chan, size_t total) {
   const size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -266,31 +240,8 @@ hipError_t launch_finalise_fused(const FusedOut* outs, int n_outs, int n_blocks,
   return hipGetLastError();
 }
 
-// k_ingest over many recordings: workgroup -> (recording, frame chunk).
-__global__ void k_ingest_fused(const FusedMask* __restrict__ masks, int n_masks) {
-  int lo = 0, hi = n_masks - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (masks[mid].blk0 <= (int)blockIdx.x)
-      lo = mid;
-    else
-      hi = mid - 1;
-  }
-  const FusedMask& K = masks[lo];
-  const int64_t f = (int64_t)((int)blockIdx.x - K.blk0) * blockDim.x + threadIdx.x;
-  if (f < K.n_frames) K.ok[f] = K.words[f * kFrameWords] == kSync ? 1 : 0;
-}
-
-int ingest_fused_blocks(int64_t n_frames) { return (int)((n_frames + 255) / 256); }
-
-hipError_t launch_ingest_fused(const FusedMask* masks, int n_masks, int n_blocks, hipStream_t s) {
-  if (n_blocks <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_ingest_fused, dim3(n_blocks), dim3(256), 0, s, masks, n_masks);
-  return hipGetLastError();
-}
-
 hipError_t launch_finalise(const double2* vacc, int n_slots, size_t slot_stride,
-                           const double* wst, int n_stations, int n_pols, float2* vis,
+                           const unsigned long long* wst, int n_stations, int n_pols, float2* vis,
                            float* weight, int n_subbands, int M, int n_chan, hipStream_t s) {
   const int nbl = M * (M + 1) / 2;
   const size_t total = (size_t)n_subbands * nbl * n_chan;

@@ -15,6 +15,18 @@
 
 namespace xc {
 
+// Add a slice's FP32 sums to its FP64 slot element; the first block of a job
+// that uses the slot stores them instead (nobody clears the slots).
+__device__ __forceinline__ void slot_update(double2* o, float re, float im, bool add) {
+  double2 v = make_double2((double)re, (double)im);
+  if (add) {
+    const double2 old = *o;
+    v.x = old.x + v.x;
+    v.y = old.y + v.y;
+  }
+  *o = v;
+}
+
 constexpr int kGroup = 4;
 
 __device__ inline void tile_of(int tile, int ng, int& gi, int& gj) {
@@ -38,7 +50,7 @@ template <int KC, int FB, int MAXL>
 __global__ void __launch_bounds__(1024)
     k_xmac(const DevJob* __restrict__ job, const float2* __restrict__ spec,
            double2* __restrict__ vacc, int nf, int tiles_per_wg, int zchunks,
-           int frames_per_split, size_t slot_stride) {
+           int frames_per_split, size_t slot_stride, int n_init) {
   extern __shared__ float4 sh4[];
   constexpr int RS = KC + 2;          // float2 per LDS row
   constexpr int RS4 = RS / 2;         // float4 per LDS row
@@ -138,17 +150,15 @@ __global__ void __launch_bounds__(1024)
   }
   if (!active || fa >= fz) return;
   double2* slot = vacc + (size_t)split * slot_stride;
+  const bool add = split < n_init;
 #pragma unroll
   for (int x = 0; x < kGroup; ++x)
 #pragma unroll
     for (int y = 0; y < kGroup; ++y) {
       const int i = gi * kGroup + x, j = gj * kGroup + y;
       if (i <= j && j < M) {
-        double2* o = slot + ((size_t)sb * nbl + bl_index(i, j, M)) * n_chan + k0 + c;
-        double2 v = *o;
-        v.x += (double)acc[x][y].x;
-        v.y += (double)acc[x][y].y;
-        *o = v;
+        slot_update(slot + ((size_t)sb * nbl + bl_index(i, j, M)) * n_chan + k0 + c,
+                    acc[x][y].x, acc[x][y].y, add);
       }
     }
 }
@@ -160,7 +170,7 @@ template <int KC>
 __global__ void __launch_bounds__(1024)
     k_xmac_direct(const DevJob* __restrict__ job, const float2* __restrict__ spec,
                   double2* __restrict__ vacc, int nf, int tiles_per_wg, int zchunks,
-                  int frames_per_split, size_t slot_stride) {
+                  int frames_per_split, size_t slot_stride, int n_init) {
   const DevJob& J = *job;
   const int M = J.M, n_chan = J.n_chan, nbl = J.nbl;
   const int Mp = (M + kGroup - 1) / kGroup * kGroup;
@@ -223,17 +233,15 @@ __global__ void __launch_bounds__(1024)
     p += fstride;
   }
   double2* slot = vacc + (size_t)split * slot_stride;
+  const bool add = split < n_init;
 #pragma unroll
   for (int x = 0; x < kGroup; ++x)
 #pragma unroll
     for (int y = 0; y < kGroup; ++y) {
       const int i = gi * kGroup + x, j = gj * kGroup + y;
       if (i <= j && j < M) {
-        double2* o = slot + ((size_t)sb * nbl + bl_index(i, j, M)) * n_chan + k0 + c;
-        double2 v = *o;
-        v.x += (double)acc[x][y].x;
-        v.y += (double)acc[x][y].y;
-        *o = v;
+        slot_update(slot + ((size_t)sb * nbl + bl_index(i, j, M)) * n_chan + k0 + c,
+                    acc[x][y].x, acc[x][y].y, add);
       }
     }
 }
@@ -312,7 +320,7 @@ template <int MP>
 __global__ void __launch_bounds__(1024)
     k_xmac_ring(const DevJob* __restrict__ job, const float2* __restrict__ spec,
                 double2* __restrict__ vacc, int nf, int tiles_per_wg, int zchunks,
-                int frames_per_split, size_t slot_stride) {
+                int frames_per_split, size_t slot_stride, int n_init) {
   static_assert(MP % kGroup == 0 && MP <= 32, "ring stages hold at most 32 inputs");
   static_assert(kRing == 8, "one LDS variable per stage");
   constexpr int KC = 64;
@@ -402,24 +410,22 @@ __global__ void __launch_bounds__(1024)
   __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
   if (!active) return;
   double2* slot = vacc + (size_t)split * slot_stride;
+  const bool add = split < n_init;
 #pragma unroll
   for (int x = 0; x < kGroup; ++x)
 #pragma unroll
     for (int y = 0; y < kGroup; ++y) {
       const int i = gi * kGroup + x, j = gj * kGroup + y;
       if (i <= j && j < M) {
-        double2* o = slot + ((size_t)sb * nbl + bl_index(i, j, M)) * n_chan + k0 + lane;
-        double2 v = *o;
-        v.x += (double)acc[x][y].x;
-        v.y += (double)acc[x][y].y;
-        *o = v;
+        slot_update(slot + ((size_t)sb * nbl + bl_index(i, j, M)) * n_chan + k0 + lane,
+                    acc[x][y].x, acc[x][y].y, add);
       }
     }
 }
 #undef XC_RING_STEP
 
 static hipError_t launch_ring(const DevJob* job, int M, int n_chan, int n_subbands,
-                              const float2* spec, double2* vacc, size_t slot_stride, int nf,
+                              const float2* spec, double2* vacc, size_t slot_stride, int n_init, int nf,
                               int fps_max, int tpw_req, hipStream_t s) {
   const int Mp = (M + kGroup - 1) / kGroup * kGroup;
   const int ng = Mp / kGroup;
@@ -437,7 +443,7 @@ static hipError_t launch_ring(const DevJob* job, int M, int n_chan, int n_subban
 #define XMAC_RING(MPV)                                                                    \
   case MPV:                                                                               \
     hipLaunchKernelGGL((k_xmac_ring<MPV>), grid, block, 0, s, job, spec, vacc, nf,        \
-                       tiles_per_wg, zchunks, fps, slot_stride);                          \
+                       tiles_per_wg, zchunks, fps, slot_stride, n_init);                          \
     break;
   switch (Mp) {
     XMAC_RING(4) XMAC_RING(8) XMAC_RING(12) XMAC_RING(16) XMAC_RING(20) XMAC_RING(24)
@@ -533,7 +539,7 @@ template <int MG, int S, int PART, int D>
 __device__ __forceinline__ void xmfma32_part(const float2* __restrict__ src,
                                              const int (&roff)[MG], size_t fstride, int fa,
                                              int fz, int M, int n_chan, int nbl, int sb, int c,
-                                             int r, double2* __restrict__ slot) {
+                                             int r, double2* __restrict__ slot, bool add) {
   constexpr MfmaTiles<MG> tiles{};
   constexpr int NT = MfmaTiles<MG>::NT;
   constexpr int NTW = (NT + S - 1) / S;
@@ -596,11 +602,8 @@ __device__ __forceinline__ void xmfma32_part(const float2* __restrict__ src,
     for (int x = 0; x < kGroup; ++x) {
       const int i = gi * kGroup + x, j = gj * kGroup + r;
       if (i <= j && j < M) {
-        double2* o = slot + ((size_t)sb * nbl + bl_index(i, j, M)) * n_chan + c;
-        double2 v = *o;
-        v.x += (double)accr[t][x];
-        v.y += (double)acci[t][x];
-        *o = v;
+        slot_update(slot + ((size_t)sb * nbl + bl_index(i, j, M)) * n_chan + c,
+                    accr[t][x], acci[t][x], add);
       }
     }
   }
@@ -611,7 +614,7 @@ __device__ __forceinline__ void xmfma32_part(const float2* __restrict__ src,
 template <int MG, int S, int D>
 __global__ void __launch_bounds__(256)
     k_xmac_mfma(const DevJob* __restrict__ job, const float2* __restrict__ spec,
-                double2* __restrict__ vacc, int nf, int frames_per_split, size_t slot_stride) {
+                double2* __restrict__ vacc, int nf, int frames_per_split, size_t slot_stride, int n_init) {
   const DevJob& J = *job;
   const int M = J.M, n_chan = J.n_chan, nbl = J.nbl;
   const int lane = threadIdx.x & 63;
@@ -631,16 +634,17 @@ __global__ void __launch_bounds__(256)
   for (int g = 0; g < MG; ++g) roff[g] = min(4 * g + r, M - 1) * n_chan;
   const size_t fstride = (size_t)M * n_chan;
   double2* slot = vacc + (size_t)split * slot_stride;
+  const bool add = split < n_init;
   static_assert(S >= 1 && S <= 3, "one to three parts per channel block");
   const int part = wave % S;
   if (part == 0)
-    xmfma32_part<MG, S, 0, D>(src, roff, fstride, fa, fz, M, n_chan, nbl, sb, c, r, slot);
+    xmfma32_part<MG, S, 0, D>(src, roff, fstride, fa, fz, M, n_chan, nbl, sb, c, r, slot, add);
   if constexpr (S >= 2)
     if (part == 1)
-      xmfma32_part<MG, S, 1, D>(src, roff, fstride, fa, fz, M, n_chan, nbl, sb, c, r, slot);
+      xmfma32_part<MG, S, 1, D>(src, roff, fstride, fa, fz, M, n_chan, nbl, sb, c, r, slot, add);
   if constexpr (S >= 3)
     if (part == 2)
-      xmfma32_part<MG, S, 2, D>(src, roff, fstride, fa, fz, M, n_chan, nbl, sb, c, r, slot);
+      xmfma32_part<MG, S, 2, D>(src, roff, fstride, fa, fz, M, n_chan, nbl, sb, c, r, slot, add);
 }
 
 // Parts per channel block and frames in flight per wave for MG groups: the
@@ -654,7 +658,7 @@ constexpr int mfma_parts(int MG) { return MG <= 6 ? 1 : 2; }
 constexpr int mfma_depth(int MG) { return MG <= 4 ? 8 : MG == 5 || MG == 7 ? 4 : 3; }
 
 static hipError_t launch_mfma(const DevJob* job, int M, int n_chan, int n_subbands,
-                              const float2* spec, double2* vacc, size_t slot_stride, int nf,
+                              const float2* spec, double2* vacc, size_t slot_stride, int n_init, int nf,
                               int fps_max, hipStream_t s) {
   const int ng = (M + kGroup - 1) / kGroup;
   if (ng > 8 || n_chan % 16 != 0) return hipErrorInvalidValue;
@@ -668,7 +672,7 @@ static hipError_t launch_mfma(const DevJob* job, int M, int n_chan, int n_subban
 #define XMAC_MFMA(NG)                                                                     \
   case NG:                                                                                \
     hipLaunchKernelGGL((k_xmac_mfma<NG, mfma_parts(NG), mfma_depth(NG)>), grid, block, 0, s,\
-                       job, spec, vacc, nf, fps, slot_stride);                            \
+                       job, spec, vacc, nf, fps, slot_stride, n_init);                    \
     break;
   switch (ng) {
     XMAC_MFMA(1) XMAC_MFMA(2) XMAC_MFMA(3) XMAC_MFMA(4) XMAC_MFMA(5) XMAC_MFMA(6)
@@ -726,7 +730,7 @@ __device__ __forceinline__ void ringm_part(float4* r0, float4* r1, float4* r2, f
                                           const float4* __restrict__ gsrc, int loff,
                                           size_t fstride4, int wbase, int rbase, int fa,
                                           int fz, int M, int n_chan, int nbl, int sb, int c,
-                                          int r, double2* __restrict__ slot) {
+                                          int r, double2* __restrict__ slot, bool add) {
   constexpr int MG = MP / kGroup;
   constexpr MfmaTiles<MG> tiles{};
   constexpr int NT = MfmaTiles<MG>::NT;
@@ -805,11 +809,8 @@ __device__ __forceinline__ void ringm_part(float4* r0, float4* r1, float4* r2, f
     for (int x = 0; x < kGroup; ++x) {
       const int i = gi * kGroup + x, jj = gj * kGroup + r;
       if (i <= jj && jj < M) {
-        double2* o = slot + ((size_t)sb * nbl + bl_index(i, jj, M)) * n_chan + c;
-        double2 v = *o;
-        v.x += (double)accr[t][x];
-        v.y += (double)acci[t][x];
-        *o = v;
+        slot_update(slot + ((size_t)sb * nbl + bl_index(i, jj, M)) * n_chan + c,
+                    accr[t][x], acci[t][x], add);
       }
     }
   }
@@ -824,7 +825,7 @@ template <int MP, bool FUSED>
 __global__ void __launch_bounds__(1024)
     k_xmac_ringm(const DevJob* __restrict__ job, const float2* __restrict__ spec,
                  double2* __restrict__ vacc, int nf, int frames_per_split, size_t slot_stride,
-                 const FusedItem* __restrict__ items, int n_items) {
+                 int n_init, const FusedItem* __restrict__ items, int n_items) {
   static_assert(MP % kGroup == 0 && MP <= 32, "ring stages hold at most 32 inputs");
   static_assert(kRing == 8, "one LDS variable per stage");
   constexpr int S = ringm_parts(MP);
@@ -842,6 +843,7 @@ __global__ void __launch_bounds__(1024)
     nf = ik[it].nf;
     frames_per_split = ik[it].fps;
     slot_stride = ik[it].slot_stride;
+    n_init = ik[it].n_init;
     const int n_ct = job->n_chan / 64;
     int local = (int)blockIdx.x - ik[it].xblk0;
     bx = local % n_ct;
@@ -875,22 +877,23 @@ __global__ void __launch_bounds__(1024)
   const int rbase = r * (kRingmPair / 8) + cb * 16 + b;
   const int c = k0 + cb * 16 + b;
   double2* slot = vacc + (size_t)split * slot_stride;
+  const bool add = split < n_init;
   static_assert(S >= 1 && S <= 4, "one to four parts");
   if (part == 0)
     ringm_part<MP, S, 0>(r0, r1, r2, r3, r4, r5, r6, r7, gsrc, loff, fstride4, wbase, rbase, fa,
-                         fz, M, n_chan, nbl, sb, c, r, slot);
+                         fz, M, n_chan, nbl, sb, c, r, slot, add);
   if constexpr (S >= 2)
     if (part == 1)
       ringm_part<MP, S, 1>(r0, r1, r2, r3, r4, r5, r6, r7, gsrc, loff, fstride4, wbase, rbase,
-                           fa, fz, M, n_chan, nbl, sb, c, r, slot);
+                           fa, fz, M, n_chan, nbl, sb, c, r, slot, add);
   if constexpr (S >= 3)
     if (part == 2)
       ringm_part<MP, S, 2>(r0, r1, r2, r3, r4, r5, r6, r7, gsrc, loff, fstride4, wbase, rbase,
-                           fa, fz, M, n_chan, nbl, sb, c, r, slot);
+                           fa, fz, M, n_chan, nbl, sb, c, r, slot, add);
   if constexpr (S >= 4)
     if (part == 3)
       ringm_part<MP, S, 3>(r0, r1, r2, r3, r4, r5, r6, r7, gsrc, loff, fstride4, wbase, rbase,
-                           fa, fz, M, n_chan, nbl, sb, c, r, slot);
+                           fa, fz, M, n_chan, nbl, sb, c, r, slot, add);
 }
 
 // Workgroups of the ring-fed matrix kernel (inputs padded to Mp) resident on
@@ -926,7 +929,7 @@ long ringm_resident(int Mp) {
 }
 
 static hipError_t launch_ringm(const DevJob* job, int M, int n_chan, int n_subbands,
-                               const float2* spec, double2* vacc, size_t slot_stride, int nf,
+                               const float2* spec, double2* vacc, size_t slot_stride, int n_init, int nf,
                                int fps_max, hipStream_t s) {
   const int Mp = (M + kGroup - 1) / kGroup * kGroup;
   if (Mp > 32 || n_chan % 64 != 0) return hipErrorInvalidValue;
@@ -937,7 +940,7 @@ static hipError_t launch_ringm(const DevJob* job, int M, int n_chan, int n_subba
 #define XMAC_RINGM(MPV)                                                                   \
   case MPV:                                                                               \
     hipLaunchKernelGGL((k_xmac_ringm<MPV, false>), grid, block, 0, s, job, spec, vacc, nf, \
-                       fps, slot_stride, nullptr, 0);                                     \
+                       fps, slot_stride, n_init, nullptr, 0);                             \
     break;
   switch (Mp) {
     XMAC_RINGM(4) XMAC_RINGM(8) XMAC_RINGM(12) XMAC_RINGM(16) XMAC_RINGM(20) XMAC_RINGM(24)
@@ -963,7 +966,7 @@ hipError_t launch_xmac_fused(int Mp, const FusedItem* items, int n_items, int n_
 #define XMAC_FUSED(MPV)                                                                   \
   case MPV:                                                                               \
     hipLaunchKernelGGL((k_xmac_ringm<MPV, true>), grid, block, 0, s, nullptr, nullptr,    \
-                       nullptr, 0, 0, 0, items, n_items);                                 \
+                       nullptr, 0, 0, 0, 0, items, n_items);                              \
     break;
   switch (Mp) {
     XMAC_FUSED(4) XMAC_FUSED(8) XMAC_FUSED(12) XMAC_FUSED(16) XMAC_FUSED(20) XMAC_FUSED(24)
@@ -975,7 +978,7 @@ hipError_t launch_xmac_fused(int Mp, const FusedItem* items, int n_items, int n_
 }
 
 static hipError_t launch_direct(const DevJob* job, int M, int n_chan, int n_subbands,
-                                const float2* spec, double2* vacc, size_t slot_stride, int nf,
+                                const float2* spec, double2* vacc, size_t slot_stride, int n_init, int nf,
                                 int fps_max, int kc_req, int tpw_req, hipStream_t s) {
   const int Mp = (M + kGroup - 1) / kGroup * kGroup;
   const int ng = Mp / kGroup;
@@ -993,15 +996,15 @@ static hipError_t launch_direct(const DevJob* job, int M, int n_chan, int n_subb
   switch (KC) {
     case 64:
       hipLaunchKernelGGL(k_xmac_direct<64>, grid, block, 0, s, job, spec, vacc, nf, tiles_per_wg,
-                         zchunks, fps, slot_stride);
+                         zchunks, fps, slot_stride, n_init);
       break;
     case 32:
       hipLaunchKernelGGL(k_xmac_direct<32>, grid, block, 0, s, job, spec, vacc, nf, tiles_per_wg,
-                         zchunks, fps, slot_stride);
+                         zchunks, fps, slot_stride, n_init);
       break;
     default:
       hipLaunchKernelGGL(k_xmac_direct<16>, grid, block, 0, s, job, spec, vacc, nf, tiles_per_wg,
-                         zchunks, fps, slot_stride);
+                         zchunks, fps, slot_stride, n_init);
       break;
   }
   return hipGetLastError();
@@ -1038,7 +1041,7 @@ int xmac_frames_per_split(int T, int M, int n_chan, int n_subbands) {
 
 template <int FB>
 static hipError_t launch_fb(const DevJob* job, int M, int n_chan, int n_subbands,
-                            const float2* spec, double2* vacc, size_t slot_stride, int nf,
+                            const float2* spec, double2* vacc, size_t slot_stride, int n_init, int nf,
                             int fps_max, int kc_req, int tpw_req, hipStream_t s) {
   const int Mp = (M + kGroup - 1) / kGroup * kGroup;
   const int ng = Mp / kGroup;
@@ -1083,7 +1086,7 @@ static hipError_t launch_fb(const DevJob* job, int M, int n_chan, int n_subbands
       if (e != hipSuccess) return e;                                                           \
     }                                                                                          \
     hipLaunchKernelGGL(kern, grid, block, lds, s, job, spec, vacc, nf, tiles_per_wg, zchunks,  \
-                       fps, slot_stride);                                                      \
+                       fps, slot_stride, n_init);                                              \
   } while (0)
   if (per_thr <= 4) {
     if (KC == 64) XMAC_LAUNCH(64, 4); else if (KC == 32) XMAC_LAUNCH(32, 4); else XMAC_LAUNCH(16, 4);
@@ -1097,7 +1100,7 @@ static hipError_t launch_fb(const DevJob* job, int M, int n_chan, int n_subbands
 }
 
 hipError_t launch_xmac(const DevJob* job, int M, int n_chan, int n_subbands,
-                       const float2* spec, double2* vacc, size_t slot_stride, int nf, int fps,
+                       const float2* spec, double2* vacc, size_t slot_stride, int n_init, int nf, int fps,
                        int fb, int kc, int tpw, hipStream_t s) {
   if (fps < 1) return hipErrorInvalidValue;
   const int Mp = (M + kGroup - 1) / kGroup * kGroup;
@@ -1107,17 +1110,17 @@ hipError_t launch_xmac(const DevJob* job, int M, int n_chan, int n_subbands,
   // and 16 equal within 2 %; the vector units are left free)
   if (fb == 0 && Mp <= 32 && kc == 0 && tpw == 0 && n_chan % 64 == 0) fb = kXmacMatrixRing;
   if ((fb == 0 || fb == kRing) && Mp <= 32 && (kc == 0 || kc == 64))
-    return launch_ring(job, M, n_chan, n_subbands, spec, vacc, slot_stride, nf, fps, tpw, s);
+    return launch_ring(job, M, n_chan, n_subbands, spec, vacc, slot_stride, n_init, nf, fps, tpw, s);
   if (fb == kXmacMatrixRing && Mp <= 32 && n_chan % 64 == 0)
-    return launch_ringm(job, M, n_chan, n_subbands, spec, vacc, slot_stride, nf, fps, s);
+    return launch_ringm(job, M, n_chan, n_subbands, spec, vacc, slot_stride, n_init, nf, fps, s);
   if (fb == kXmacMatrix && Mp <= 32 && n_chan % 16 == 0)
-    return launch_mfma(job, M, n_chan, n_subbands, spec, vacc, slot_stride, nf, fps, s);
+    return launch_mfma(job, M, n_chan, n_subbands, spec, vacc, slot_stride, n_init, nf, fps, s);
   if (fb == 1)
-    return launch_direct(job, M, n_chan, n_subbands, spec, vacc, slot_stride, nf, fps, kc, tpw,
+    return launch_direct(job, M, n_chan, n_subbands, spec, vacc, slot_stride, n_init, nf, fps, kc, tpw,
                          s);
   if (fb == 4)
-    return launch_fb<4>(job, M, n_chan, n_subbands, spec, vacc, slot_stride, nf, fps, kc, tpw, s);
-  return launch_fb<2>(job, M, n_chan, n_subbands, spec, vacc, slot_stride, nf, fps, kc, tpw, s);
+    return launch_fb<4>(job, M, n_chan, n_subbands, spec, vacc, slot_stride, n_init, nf, fps, kc, tpw, s);
+  return launch_fb<2>(job, M, n_chan, n_subbands, spec, vacc, slot_stride, n_init, nf, fps, kc, tpw, s);
 }
 
 }  // namespace xc

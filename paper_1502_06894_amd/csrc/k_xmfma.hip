@@ -92,7 +92,7 @@ __device__ inline int bl_of(int i, int j, int M) { return i * M - (i * (i - 1)) 
 template <int OUT, int KC, int CPW, int FB>
 __global__ void __launch_bounds__(64 * (KC / CPW))
     k_xmfma(const DevJob* __restrict__ job, const uint32_t* __restrict__ spec,
-            const int8_t* __restrict__ scale_exp, double2* __restrict__ vacc, int nf) {
+            const int8_t* __restrict__ scale_exp, double2* __restrict__ vacc, int nf, bool add) {
   constexpr int NW = KC / CPW;                       // waves
   constexpr int NT = 64 * NW;
   constexpr int RW = OUT == kOutF16 ? KC : KC / 2;   // 32-bit words per (frame, input) row
@@ -246,9 +246,12 @@ __global__ void __launch_bounds__(64 * (KC / CPW))
         const double re = (double)accre[c][v] * sc;
         const double im = ((double)acc21[c][v] - (double)scr[j * 33 + i]) * sc;
         double2* o = vacc + ((size_t)sb * nbl + bl_of(i, j, M)) * n_chan + k;
-        double2 a = *o;
-        a.x += re;
-        a.y += im;
+        double2 a = make_double2(re, im);
+        if (add) {           // (a job's first block stores)
+          const double2 old = *o;
+          a.x = old.x + re;
+          a.y = old.y + im;
+        }
         *o = a;
       }
     }
@@ -258,7 +261,7 @@ __global__ void __launch_bounds__(64 * (KC / CPW))
 
 template <int OUT, int KC, int CPW, int FB>
 static hipError_t launch_cfg(const DevJob* job, int n_chan, int n_subbands, const void* spec,
-                             const int8_t* scale_exp, double2* vacc, int nf, hipStream_t s) {
+                             const int8_t* scale_exp, double2* vacc, int nf, bool add, hipStream_t s) {
   constexpr int NW = KC / CPW;
   constexpr int RW = OUT == kOutF16 ? KC : KC / 2;
   size_t lds = 2 * (OUT == kOutF16 ? (size_t)FB * (32 * (RW + 1) + 1)
@@ -280,14 +283,14 @@ static hipError_t launch_cfg(const DevJob* job, int n_chan, int n_subbands, cons
   }
   dim3 grid(n_chan / KC, n_subbands);
   hipLaunchKernelGGL((k_xmfma<OUT, KC, CPW, FB>), grid, dim3(64 * NW), lds, s, job,
-                     static_cast<const uint32_t*>(spec), scale_exp, vacc, nf);
+                     static_cast<const uint32_t*>(spec), scale_exp, vacc, nf, add);
   return hipGetLastError();
 }
 
 hipError_t launch_xmfma(const DevJob* job, int out, int M, int n_chan, int n_subbands,
                         const void* spec, const int8_t* scale_exp, double2* vacc,
-                        size_t slot_stride, int nf, hipStream_t s) {
-  (void)slot_stride;
+                        int n_init, int nf, hipStream_t s) {
+  const bool add = n_init > 0;
   if (M > 32 || n_chan < 32) return hipErrorInvalidValue;
   // 16 channels per workgroup, one per wave (16 waves, 110 registers: four
   // waves per SIMD); 32 (FP16) / 64 (e4m3) frames per LDS stage, 139 KB of LDS,
@@ -295,9 +298,9 @@ hipError_t launch_xmfma(const DevJob* job, int out, int M, int n_chan, int n_sub
   // FP16 5.33 -> 5.07 ms, e4m3 4.42 -> 3.86 ms; two channels per wave (8 waves)
   // -> one, 5.07 -> 4.87 and 3.88 -> 3.70 ms.
   if (out == kOutF16)
-    return launch_cfg<kOutF16, 16, 1, 32>(job, n_chan, n_subbands, spec, scale_exp, vacc, nf, s);
+    return launch_cfg<kOutF16, 16, 1, 32>(job, n_chan, n_subbands, spec, scale_exp, vacc, nf, add, s);
   if (out == kOutF8)
-    return launch_cfg<kOutF8, 16, 1, 64>(job, n_chan, n_subbands, spec, scale_exp, vacc, nf, s);
+    return launch_cfg<kOutF8, 16, 1, 64>(job, n_chan, n_subbands, spec, scale_exp, vacc, nf, add, s);
   return hipErrorInvalidValue;
 }
 

@@ -121,10 +121,10 @@ void xc_server::start(Request& r) {
   unsigned char* desc = pool_base + r.off;
   unsigned char* arena = desc + align_up(r.L.desc_bytes);
   hipStream_t s = ctx->lanes[lane];
-  int rc = upload_desc(ctx, &r.setup, r.st.data(), r.L, desc, arena, s);
+  int rc = upload_desc(ctx, &r.setup, r.st.data(), r.L, desc, s);
   if (rc == XC_OK)
     rc = enqueue_job(ctx, &r.setup, r.st.data(), &r.out, reinterpret_cast<const DevJob*>(desc),
-                     arena, r.L, r.tu, s);
+                     arena, r.L, r.tu, true, s);
   if (rc == XC_OK && hipEventRecord(r.done_ev, s) != hipSuccess) rc = XC_E_HIP;
   r.rc = rc;
   if (rc != XC_OK) last_error = ctx->last_error;

@@ -19,7 +19,7 @@ constexpr int kTwiddleN = 32768;      // twiddle table length: exp(-2 pi i m / 3
 
 struct DevStation {
   const uint32_t* words;      // recording, kFrameWords per frame
-  const uint8_t* frame_ok;    // per recording frame: 1 = good sync
+  const uint8_t* frame_ok;    // per recording frame: 1 = good sync (null: read the sync words)
   int64_t n_frames_m5b;
   int64_t first_sample;
   int32_t poly_deg;

@@ -23,15 +23,15 @@ struct FusedItem {
   PhaseRec* prec;          // [S][n_sb][nf]
   float2* spec;            // [n_sb][nf][M][n_chan]
   double2* vacc;           // the job's FP64 accumulator slots
-  double* wst;             // the job's station-pair weights [S][S]
+  unsigned long long* wst; // the job's station-pair weights [S][S]
   size_t slot_stride;      // double2 elements per slot
   int64_t f0;              // first frame of the block
   int32_t nf;              // frames in the block
   int32_t fps;             // X stage: frames per FP32 slice
   int32_t spt;             // matrix-core F stage: subbands per task
+  int32_t n_init;          // X stage: accumulator slots already written
   int32_t task0;           // F stage: tasks before this item
   int32_t dblk0;           // delay kernel: workgroups before this item
-  int32_t wblk0;           // weight kernel: workgroups before this item
   int32_t xblk0;           // X stage: workgroups before this item in its launch
 };
 
@@ -60,12 +60,15 @@ __device__ inline FusedItemsK fused_const(const FusedItem* items) { return (Fuse
 // A0: frame_ok[f] = sync word of recording frame f is good.
 hipError_t launch_ingest(const uint32_t* words, int64_t n_frames, uint8_t* frame_ok,
                          hipStream_t s);
-// Zero n doubles.
-hipError_t launch_zero(double* p, size_t n, hipStream_t s);
+// Zero n 64-bit words.
+hipError_t launch_zero(unsigned long long* p, size_t n, hipStream_t s);
 // A1: delay and phase records for frames f0 .. f0+nf-1 of every station; also
-// zeroes the F stage's task counter *ctr when ctr is not null.
+// zeroes the F stage's task counters ctr[0], ctr[1] when ctr is not null and,
+// when wst is not null, adds the number of frames valid for both stations of
+// each station pair si <= sj to wst[si][sj].
 hipError_t launch_delays(const DevJob* job, int n_stations, int n_subbands, int64_t f0, int nf,
-                         DelayRec* drec, PhaseRec* prec, unsigned* ctr, hipStream_t s);
+                         DelayRec* drec, PhaseRec* prec, unsigned* ctr, unsigned long long* wst,
+                         hipStream_t s);
 // A2-A5: spectra [n_subbands][nf][M][n_chan] for the block's frames (FP32;
 // the low-precision ones channel-blocked, see lp_index).
 // Spectrum element types written by the F stage.
@@ -172,8 +175,8 @@ hipError_t launch_scales(const float2* spec, const DelayRec* drec, int n_subband
 // A7: X stage on MFMA for the low-precision spectra (out = kOutF16 or kOutF8),
 // M <= 32; accumulates into the same FP64 slots as the FP32 X stage.
 hipError_t launch_xmfma(const DevJob* job, int out, int M, int n_chan, int n_subbands,
-                        const void* spec, const int8_t* scale_exp, double2* vacc,
-                        size_t slot_stride, int nf, hipStream_t s);
+                        const void* spec, const int8_t* scale_exp, double2* vacc, int n_init,
+                        int nf, hipStream_t s);
 // Frames (at most) one X workgroup accumulates in FP32 before adding to its
 // FP64 slot, for blocks of T frames of a job with M inputs per subband: up to
 // 1024 (balanced so that the ring-fed matrix kernel's workgroups fill whole
@@ -182,6 +185,7 @@ hipError_t launch_xmfma(const DevJob* job, int out, int M, int n_chan, int n_sub
 int xmac_frames_per_split(int T, int M, int n_chan, int n_subbands);
 // A6: accumulate the block's spectra into the FP64 slots vacc[split][n_sb][nbl][n_chan]
 // (double2), slot_stride elements apart; fps: xmac_frames_per_split of the job.
+// Slots below n_init are added to, the others (not yet written) stored.
 // fb: staging (8 = LDS ring, 2 or 4 = register-staged stages, 1 = none,
 // kXmacMatrix = FP32 products on the matrix cores with operands loaded per
 // wave, kXmacMatrixRing = the same products fed through the LDS ring, 0 =
@@ -191,27 +195,23 @@ int xmac_frames_per_split(int T, int M, int n_chan, int n_subbands);
 constexpr int kXmacMatrix = 3;
 constexpr int kXmacMatrixRing = 5;
 hipError_t launch_xmac(const DevJob* job, int M, int n_chan, int n_subbands,
-                       const float2* spec, double2* vacc, size_t slot_stride, int nf, int fps,
+                       const float2* spec, double2* vacc, size_t slot_stride, int n_init, int nf,
+                       int fps,
                        int fb, int kc, int tpw, hipStream_t s);
-// Frames of the block valid for both stations of each station pair: wst[si][sj] += count.
-hipError_t launch_weights(const DelayRec* drec, int n_stations, int nf, double* wst,
-                          hipStream_t s);
 // A8: vis = (sum of the n_slots slots) / W (W = 0 -> 0), weight = W, with W of
 // baseline (i, j) taken from wst[i / P][j / P].
 hipError_t launch_finalise(const double2* vacc, int n_slots, size_t slot_stride,
-                           const double* wst, int n_stations, int n_pols, float2* vis,
+                           const unsigned long long* wst, int n_stations, int n_pols, float2* vis,
                            float* weight, int n_subbands, int M, int n_chan, hipStream_t s);
 // Fused batches (FP32 spectra, the regular F-stage variants 0, kFstageLean and
 // kFstageShare; no drift-correction pass).  `items` is a device table of
 // n_items FusedItem; ctr a zeroed counter (launch_delays_fused clears it).
-// Delay and phase records of every item's block (+ clears ctr[0], ctr[1]).
+// Delay and phase records and station-pair weights of every item's block (+ clears
+// ctr[0], ctr[1]).
 hipError_t launch_delays_fused(const FusedItem* items, int n_items, int n_blocks, unsigned* ctr,
                                hipStream_t s);
-// Workgroups launch_delays_fused needs for an item of nf frames, S stations, n_sb subbands.
-int delays_fused_blocks(int nf, int n_stations, int n_subbands);
-// Station-pair weights of every item's block, added to the item's job's wst.
-hipError_t launch_weights_fused(const FusedItem* items, int n_items, int n_blocks, hipStream_t s);
-int weights_fused_blocks(int nf, int n_stations);
+// Workgroups launch_delays_fused needs for an item of nf frames and n_sb subbands.
+int delays_fused_blocks(int nf, int n_subbands);
 // F stage over every item's block (all items of FFT length N, variant `waves`).
 hipError_t launch_fstage_fused(int N, int waves, const FusedItem* items, int n_items,
                                int n_tasks, const float2* tw, unsigned* ctr, hipStream_t s);
@@ -237,7 +237,7 @@ bool xmac_fused_ok(int M, int n_chan);
 // One job of a fused batch's finalise (blk0: workgroups before it).
 struct FusedOut {
   const double2* vacc;
-  const double* wst;
+  const unsigned long long* wst;
   float2* vis;
   float* weight;
   size_t slot_stride;
@@ -245,16 +245,6 @@ struct FusedOut {
 };
 hipError_t launch_finalise_fused(const FusedOut* outs, int n_outs, int n_blocks, hipStream_t s);
 int finalise_fused_blocks(int n_subbands, int M, int n_chan);
-// One recording of a fused batch's ingest (blk0: workgroups before it).
-struct FusedMask {
-  const uint32_t* words;
-  uint8_t* ok;
-  int64_t n_frames;
-  int32_t blk0;
-};
-hipError_t launch_ingest_fused(const FusedMask* masks, int n_masks, int n_blocks, hipStream_t s);
-int ingest_fused_blocks(int64_t n_frames);
-
 // Test tap: unpacked levels of one (station, input, block frame).
 hipError_t launch_debug_unpack(const DevJob* job, const DelayRec* drec, int nf, int station,
                                int input, int fl, float* out, int N, hipStream_t s);

@@ -97,8 +97,8 @@ hipError_t timed(xc_ctx* c, int kind, hipStream_t s, Fn&& fn) {
 // Per-job arena: everything a job needs besides its descriptor.
 struct Layout {
   size_t desc_bytes = 0;          // descriptor size (stored outside the arena)
-  size_t mask = 0, drec = 0, prec = 0, spec = 0, sexp = 0, vacc = 0, wacc = 0, total = 0;
-  std::vector<size_t> mask_off;   // per station, SIZE_MAX if the caller supplies frame_ok
+  size_t wst = 0, wst_bytes = 0;  // station-pair weights, first in the arena
+  size_t drec = 0, prec = 0, spec = 0, sexp = 0, vacc = 0, total = 0;
   int T = 0;                      // frames per block
   int out = kOutF32;              // spectrum element type written by the F stage
   int n_scale = 0;                // frames of the scale pre-pass (MFMA path)
@@ -128,23 +128,28 @@ Layout layout_of(const xc_setup* s, const xc_station* st, const xc_tuning& tu,
 // that traffic stays within 1/8 of the spectra's.  Returns L.T when it fits.
 constexpr int kSlotAmortize = 16;
 int shared_block_frames(const xc_setup& s, const Layout& L, size_t cap_bytes, int min_frames);
-// Descriptor for device address `dev_desc`; stations' frame_ok default to the arena masks.
+// Descriptor for device address `dev_desc`.
 void build_desc(const xc_setup* s, const xc_station* st, const Layout& L,
-                const unsigned char* dev_desc, const unsigned char* arena, unsigned char* h);
-// Stage one descriptor through a pinned ring slot and copy it to dev_desc.
+                const unsigned char* dev_desc, unsigned char* h);
+// Stage one descriptor, and zeros for the arena's weights that follow it,
+// through a pinned ring slot and copy them to dev_desc (the arena starts
+// align_up(L.desc_bytes) after it).
 int upload_desc(xc_ctx* c, const xc_setup* s, const xc_station* st, const Layout& L,
-                unsigned char* dev_desc, const unsigned char* arena, hipStream_t stream);
-// Enqueue every kernel of one job (ingest .. finalise) on `stream`; with two
-// block buffers and `xs` given, the X stages run on `xs` (joined back to
-// `stream` before the finalise).
+                unsigned char* dev_desc, hipStream_t stream);
 // Does any station ask for the drift correction inside frames?
 bool any_rate_correct(const xc_setup* s, const xc_station* st);
+// Accumulator slots that the X stage writes for a block of nf frames.
+int slots_used(int nf, int fps_max, int M, int n_chan, int n_subbands);
 // Can the job's F stage run on the matrix cores (N <= 16384, and a fringe phase
 // whose curvature inside a frame is small enough for that kernel)?
 bool fstage_matrix_ok(const xc_setup* s, const xc_station* st);
+// Enqueue every kernel of one job (delays .. finalise) on `stream`; with two
+// block buffers and `xs` given, the X stages run on `xs` (joined back to
+// `stream` before the finalise).  wst_clear: the arena's weights are zero
+// already (upload_desc); else they are cleared first.
 int enqueue_job(xc_ctx* c, const xc_setup* s, const xc_station* st, const xc_output* out,
                 const DevJob* dj, unsigned char* arena, const Layout& L, const xc_tuning& tu,
-                hipStream_t stream, hipStream_t xs = nullptr);
+                bool wst_clear, hipStream_t stream, hipStream_t xs = nullptr);
 int ensure_lanes(xc_ctx* c, int n);
 // The context's X-stage stream and block events (created on first use).
 int ensure_xstream(xc_ctx* c);

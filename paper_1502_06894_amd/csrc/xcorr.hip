@@ -2,6 +2,7 @@
 // upload and launch sequencing of the correlation path.
 #include <math.h>
 
+#include <algorithm>
 #include <atomic>
 #include <mutex>
 
@@ -201,13 +202,9 @@ Layout layout_of(const xc_setup* s, const xc_station* st, const xc_tuning& tu, b
   L.desc_bytes = sizeof(DevJob) + (size_t)S * sizeof(DevStation) +
                  (size_t)S * nsb * (kMaxPolyDeg + 1) * sizeof(double);
   size_t off = 0;
-  L.mask = off;
-  L.mask_off.assign(S, SIZE_MAX);
-  for (int i = 0; i < S; ++i)
-    if (!st[i].frame_ok) {
-      L.mask_off[i] = off - L.mask;
-      off += align_up((size_t)st[i].n_frames_m5b);
-    }
+  L.wst = off;
+  L.wst_bytes = align_up((size_t)S * S * sizeof(unsigned long long));
+  off += L.wst_bytes;
   L.nbuf = overlap && tu.block_overlap == 2 && s->n_frames > L.T ? 2 : 1;
   // each delay-record buffer ends with the F stage's task counter
   L.ctr_off = align_up((size_t)S * L.T * sizeof(DelayRec));
@@ -235,9 +232,7 @@ Layout layout_of(const xc_setup* s, const xc_station* st, const xc_tuning& tu, b
   L.n_slots = L.out == kOutF32 ? (L.T + L.fps - 1) / L.fps : 1;
   L.slot_stride = (size_t)nsb * nbl * s->n_chan;
   L.vacc = off;
-  off += (size_t)L.n_slots * L.slot_stride * sizeof(double2);   // wacc follows directly
-  L.wacc = off;
-  off += align_up((size_t)S * S * sizeof(double));
+  off += align_up((size_t)L.n_slots * L.slot_stride * sizeof(double2));
   L.total = off;
   return L;
 }
@@ -257,7 +252,7 @@ int shared_block_frames(const xc_setup& s, const Layout& L, size_t cap_bytes, in
 
 // Build the job descriptor for device address `dev` into host memory `h`.
 void build_desc(const xc_setup* s, const xc_station* st, const Layout& L,
-                const unsigned char* dev_desc, const unsigned char* arena, unsigned char* h) {
+                const unsigned char* dev_desc, unsigned char* h) {
   const int S = s->n_stations, nsb = s->n_subbands;
   DevJob* J = reinterpret_cast<DevJob*>(h);
   memset(h, 0, L.desc_bytes);
@@ -287,8 +282,7 @@ void build_desc(const xc_setup* s, const xc_station* st, const Layout& L,
   for (int i = 0; i < S; ++i) {
     DevStation& d = hs[i];
     d.words = static_cast<const uint32_t*>(st[i].frames);
-    d.frame_ok = st[i].frame_ok ? st[i].frame_ok
-                                : reinterpret_cast<const uint8_t*>(arena + L.mask + L.mask_off[i]);
+    d.frame_ok = st[i].frame_ok;
     d.n_frames_m5b = st[i].n_frames_m5b;
     d.first_sample = st[i].first_sample;
     d.poly_deg = st[i].poly_deg;
@@ -305,24 +299,32 @@ void build_desc(const xc_setup* s, const xc_station* st, const Layout& L,
 }
 
 int upload_desc(xc_ctx* c, const xc_setup* s, const xc_station* st, const Layout& L,
-                unsigned char* dev_desc, const unsigned char* arena, hipStream_t stream) {
-  if (L.desc_bytes > kSlotBytes) return fail(c, XC_E_INVAL, "descriptor too large");
+                unsigned char* dev_desc, hipStream_t stream) {
+  const size_t arena_off = align_up(L.desc_bytes), bytes = arena_off + L.wst_bytes;
+  if (bytes > kSlotBytes) return fail(c, XC_E_INVAL, "descriptor too large");
   const int k = c->next_slot;
   c->next_slot = (k + 1) % kSlots;
   hipError_t e = hipEventSynchronize(c->ev[k]);
   if (e != hipSuccess) return hip_fail(c, e, "hipEventSynchronize");
   unsigned char* h = c->h_stage + (size_t)k * kSlotBytes;
-  build_desc(s, st, L, dev_desc, arena, h);
-  e = hipMemcpyAsync(dev_desc, h, L.desc_bytes, hipMemcpyHostToDevice, stream);
+  build_desc(s, st, L, dev_desc, h);
+  memset(h + arena_off, 0, L.wst_bytes);
+  e = hipMemcpyAsync(dev_desc, h, bytes, hipMemcpyHostToDevice, stream);
   if (e != hipSuccess) return hip_fail(c, e, "descriptor upload");
   e = hipEventRecord(c->ev[k], stream);
   if (e != hipSuccess) return hip_fail(c, e, "hipEventRecord");
   return XC_OK;
 }
 
+int slots_used(int nf, int fps_max, int M, int n_chan, int n_subbands) {
+  int n = 0, fps = 0;
+  xmac_splits(nf, fps_max, M, n_chan, n_subbands, n, fps);
+  return fps > 0 ? (nf + fps - 1) / fps : 0;
+}
+
 int enqueue_job(xc_ctx* c, const xc_setup* s, const xc_station* st, const xc_output* out,
                 const DevJob* dj, unsigned char* arena, const Layout& L, const xc_tuning& tu,
-                hipStream_t stream, hipStream_t xs) {
+                bool wst_clear, hipStream_t stream, hipStream_t xs) {
   DelayRec* drec = reinterpret_cast<DelayRec*>(arena + L.drec);
   PhaseRec* prec = reinterpret_cast<PhaseRec*>(arena + L.prec);
   void* spec = arena + L.spec;
@@ -330,27 +332,20 @@ int enqueue_job(xc_ctx* c, const xc_setup* s, const xc_station* st, const xc_out
   const bool rate_pass = any_rate_correct(s, st);
   const bool mat = fstage_matrix_ok(s, st);
   double2* vacc = reinterpret_cast<double2*>(arena + L.vacc);
-  double* wacc = reinterpret_cast<double*>(arena + L.wacc);
+  unsigned long long* wst = reinterpret_cast<unsigned long long*>(arena + L.wst);
   int8_t* sexp = reinterpret_cast<int8_t*>(arena + L.sexp);
   const int S = s->n_stations, nsb = s->n_subbands, M = S * s->n_pols;
   const int N = 2 * s->n_chan;
   hipError_t e = hipSuccess;
-  for (int i = 0; i < S && e == hipSuccess; ++i)
-    if (!st[i].frame_ok)
-      e = timed(c, XC_K_INGEST, stream, [&] {
-        return launch_ingest(static_cast<const uint32_t*>(st[i].frames), st[i].n_frames_m5b,
-                             reinterpret_cast<uint8_t*>(arena + L.mask + L.mask_off[i]), stream);
-      });
-  if (e != hipSuccess) return hip_fail(c, e, "ingest");
-  e = timed(c, XC_K_ZERO, stream, [&] {
-    return launch_zero(reinterpret_cast<double*>(vacc), (L.total - L.vacc) / sizeof(double),
-                       stream);
-  });
+  if (!wst_clear)
+    e = timed(c, XC_K_ZERO, stream, [&] {
+      return launch_zero(wst, L.wst_bytes / sizeof(unsigned long long), stream);
+    });
   if (e != hipSuccess) return hip_fail(c, e, "zero");
   if (L.out != kOutF32) {
     // channel scales from the first frames' FP32 spectra
     unsigned* ctr0 = reinterpret_cast<unsigned*>(arena + L.drec + L.ctr_off);
-    e = launch_delays(dj, S, nsb, 0, L.n_scale, drec, prec, ctr0, stream);
+    e = launch_delays(dj, S, nsb, 0, L.n_scale, drec, prec, ctr0, nullptr, stream);
     if (e == hipSuccess)
       e = timed(c, XC_K_FSTAGE, stream, [&] {
         return launch_fstage(N, dj, S, nsb, nsb * s->n_pols, drec, prec, c->d_tw, spec, nullptr,
@@ -367,6 +362,7 @@ int enqueue_job(xc_ctx* c, const xc_setup* s, const xc_station* st, const xc_out
   // stage (on `stream`) waits until the X stage of block b - 2 (on `xs`) has
   // read that buffer, and its X stage waits for its F stage.
   int64_t blk = 0;
+  int n_init = 0;     // accumulator slots written so far
   for (int64_t f0 = 0; f0 < s->n_frames; f0 += L.T, ++blk) {
     const int nf = (int)((s->n_frames - f0) < L.T ? (s->n_frames - f0) : L.T);
     const int p = overlap ? (int)(blk & 1) : 0;
@@ -380,8 +376,7 @@ int enqueue_job(xc_ctx* c, const xc_setup* s, const xc_station* st, const xc_out
       if (e != hipSuccess) return hip_fail(c, e, "block wait");
     }
     e = timed(c, XC_K_DELAYS, stream, [&] {
-      hipError_t r = launch_delays(dj, S, nsb, f0, nf, drec_p, prec_p, ctr_p, stream);
-      return r == hipSuccess ? launch_weights(drec_p, S, nf, wacc, stream) : r;
+      return launch_delays(dj, S, nsb, f0, nf, drec_p, prec_p, ctr_p, wst, stream);
     });
     if (e != hipSuccess) return hip_fail(c, e, "delays");
     e = timed(c, XC_K_FSTAGE, stream, [&] {
@@ -408,16 +403,16 @@ int enqueue_job(xc_ctx* c, const xc_setup* s, const xc_station* st, const xc_out
     if (L.out == kOutF32) {
       e = timed(c, XC_K_XMAC, xstr, [&] {
         return launch_xmac(dj, M, s->n_chan, nsb, static_cast<const float2*>(spec_p), vacc,
-                           L.slot_stride, nf, L.fps, tu.xmac_frames_per_stage,
+                           L.slot_stride, n_init, nf, L.fps, tu.xmac_frames_per_stage,
                            tu.xmac_channels_per_wg, tu.xmac_tiles_per_wg, xstr);
       });
     } else {
       e = timed(c, XC_K_XMFMA, xstr, [&] {
-        return launch_xmfma(dj, L.out, M, s->n_chan, nsb, spec_p, sexp, vacc, L.slot_stride, nf,
-                            xstr);
+        return launch_xmfma(dj, L.out, M, s->n_chan, nsb, spec_p, sexp, vacc, n_init, nf, xstr);
       });
     }
     if (e != hipSuccess) return hip_fail(c, e, "xmac");
+    n_init = std::max(n_init, L.out == kOutF32 ? slots_used(nf, L.fps, M, s->n_chan, nsb) : 1);
     if (overlap) {
       e = hipEventRecord(c->blk_x[p], xs);
       if (e != hipSuccess) return hip_fail(c, e, "block record");
@@ -429,7 +424,7 @@ int enqueue_job(xc_ctx* c, const xc_setup* s, const xc_station* st, const xc_out
     if (e != hipSuccess) return hip_fail(c, e, "block join");
   }
   e = timed(c, XC_K_FINALISE, stream, [&] {
-    return launch_finalise(vacc, L.n_slots, L.slot_stride, wacc, S, s->n_pols,
+    return launch_finalise(vacc, n_init, L.slot_stride, wst, S, s->n_pols,
                            static_cast<float2*>(out->vis), out->weight, nsb, M, s->n_chan,
                            stream);
   });
@@ -487,21 +482,7 @@ int prepare(xc_ctx* c, const xc_setup* s, const xc_station* st, void* workspace,
   if (e != hipSuccess) return hip_fail(c, e, "hipSetDevice");
   p.desc = static_cast<unsigned char*>(workspace);
   p.arena = p.desc + align_up(p.L.desc_bytes);
-  return upload_desc(c, s, st, p.L, p.desc, p.arena, stream);
-}
-
-// Ingest masks of stations without a caller-supplied frame_ok (taps only; the
-// correlation path does this inside enqueue_job).
-int ingest_missing(xc_ctx* c, const xc_setup* s, const xc_station* st, const Prepared& p,
-                   hipStream_t stream) {
-  for (int i = 0; i < s->n_stations; ++i)
-    if (!st[i].frame_ok) {
-      hipError_t e =
-          launch_ingest(static_cast<const uint32_t*>(st[i].frames), st[i].n_frames_m5b,
-                        reinterpret_cast<uint8_t*>(p.arena + p.L.mask + p.L.mask_off[i]), stream);
-      if (e != hipSuccess) return hip_fail(c, e, "ingest");
-    }
-  return XC_OK;
+  return upload_desc(c, s, st, p.L, p.desc, stream);
 }
 
 }  // namespace
@@ -626,7 +607,7 @@ int xc_correlate_subint(xc_ctx* c, const xc_setup* s, const xc_station* st, cons
     rc = ensure_xstream(c);
     if (rc != XC_OK) return rc;
   }
-  return enqueue_job(c, s, st, out, reinterpret_cast<const DevJob*>(p.desc), p.arena, p.L, p.tu,
+  return enqueue_job(c, s, st, out, reinterpret_cast<const DevJob*>(p.desc), p.arena, p.L, p.tu, true,
                      stream, p.L.nbuf == 2 ? c->xstream : nullptr);
 }
 
@@ -683,9 +664,9 @@ int xc_correlate_subint_noalloc(xc_ctx* c, const xc_setup* s, const xc_station* 
   if (e != hipSuccess) return hip_fail(c, e, "hipSetDevice");
   unsigned char* desc = base;
   unsigned char* arena = base + align_up(L.desc_bytes);
-  rc = upload_desc(c, &q, st, L, desc, arena, stream);
+  rc = upload_desc(c, &q, st, L, desc, stream);
   if (rc != XC_OK) return rc;
-  return enqueue_job(c, &q, st, out, reinterpret_cast<const DevJob*>(desc), arena, L, tu, stream);
+  return enqueue_job(c, &q, st, out, reinterpret_cast<const DevJob*>(desc), arena, L, tu, true, stream);
 }
 
 size_t xc_noalloc_scratch_bytes(void) { return kScratchBytes; }
@@ -755,7 +736,6 @@ int xc_debug_delays(xc_ctx* c, const xc_setup* s, const xc_station* st, int64_t*
   hipStream_t stream = (hipStream_t)stream_;
   Prepared p;
   int rc = prepare(c, s, st, workspace, ws_bytes, stream, p);
-  if (rc == XC_OK) rc = ingest_missing(c, s, st, p, stream);
   if (rc != XC_OK) return rc;
   const Layout& L = p.L;
   const DevJob* dj = reinterpret_cast<const DevJob*>(p.desc);
@@ -767,7 +747,7 @@ int xc_debug_delays(xc_ctx* c, const xc_setup* s, const xc_station* st, int64_t*
   std::vector<PhaseRec> hp((size_t)S * nsb * L.T);
   for (int64_t f0 = 0; f0 < F; f0 += L.T) {
     const int nf = (int)((F - f0) < L.T ? (F - f0) : L.T);
-    hipError_t e = launch_delays(dj, S, nsb, f0, nf, drec, prec, nullptr, stream);
+    hipError_t e = launch_delays(dj, S, nsb, f0, nf, drec, prec, nullptr, nullptr, stream);
     if (e == hipSuccess)
       e = hipMemcpyAsync(hd.data(), drec, sizeof(DelayRec) * S * nf, hipMemcpyDeviceToHost,
                          stream);
@@ -797,7 +777,6 @@ int xc_debug_unpack(xc_ctx* c, const xc_setup* s, const xc_station* st, int32_t 
   hipStream_t stream = (hipStream_t)stream_;
   Prepared p;
   int rc = prepare(c, s, st, workspace, ws_bytes, stream, p);
-  if (rc == XC_OK) rc = ingest_missing(c, s, st, p, stream);
   if (rc != XC_OK) return rc;
   if (station < 0 || station >= s->n_stations || input < 0 ||
       input >= s->n_subbands * s->n_pols || frame < 0 || frame >= s->n_frames || !out)
@@ -808,7 +787,7 @@ int xc_debug_unpack(xc_ctx* c, const xc_setup* s, const xc_station* st, int32_t 
   float* tmp = reinterpret_cast<float*>(p.arena + p.L.spec);
   const int N = 2 * s->n_chan;
   hipError_t e =
-      launch_delays(dj, s->n_stations, s->n_subbands, frame, 1, drec, prec, nullptr, stream);
+      launch_delays(dj, s->n_stations, s->n_subbands, frame, 1, drec, prec, nullptr, nullptr, stream);
   if (e == hipSuccess) e = launch_debug_unpack(dj, drec, 1, station, input, 0, tmp, N, stream);
   if (e == hipSuccess)
     e = hipMemcpyAsync(out, tmp, sizeof(float) * N, hipMemcpyDeviceToHost, stream);
@@ -821,7 +800,6 @@ int xc_debug_spectra(xc_ctx* c, const xc_setup* s, const xc_station* st, int64_t
   hipStream_t stream = (hipStream_t)stream_;
   Prepared p;
   int rc = prepare(c, s, st, workspace, ws_bytes, stream, p);
-  if (rc == XC_OK) rc = ingest_missing(c, s, st, p, stream);
   if (rc != XC_OK) return rc;
   if (n < 1 || n > p.L.T || frame0 < 0 || frame0 + n > s->n_frames || !spectra)
     return fail(c, XC_E_INVAL, "debug_spectra: frame range");
@@ -829,7 +807,8 @@ int xc_debug_spectra(xc_ctx* c, const xc_setup* s, const xc_station* st, int64_t
   DelayRec* drec = reinterpret_cast<DelayRec*>(p.arena + p.L.drec);
   PhaseRec* prec = reinterpret_cast<PhaseRec*>(p.arena + p.L.prec);
   unsigned* ctr = reinterpret_cast<unsigned*>(p.arena + p.L.drec + p.L.ctr_off);
-  hipError_t e = launch_delays(dj, s->n_stations, s->n_subbands, frame0, n, drec, prec, ctr, stream);
+  hipError_t e = launch_delays(dj, s->n_stations, s->n_subbands, frame0, n, drec, prec, ctr, nullptr,
+                               stream);
   if (e == hipSuccess)
     e = launch_fstage(2 * s->n_chan, dj, s->n_stations, s->n_subbands,
                       s->n_subbands * s->n_pols, drec, prec, c->d_tw, spectra, nullptr, n,
