@@ -36,11 +36,18 @@
 // Above, lane = the row k1 + 16 k2: both remaining passes address LDS without
 // conflicts.  Four waves share a matrix; it is formed once per subband.
 //
+// At N = 32768 the first radix is 32 (T = N / 32, e < 32), in two passes of 16 k1
+// over the same codes: a pass's exchange fits LDS, and its stores are whole
+// 128-byte lines.  (Folding the frame's halves into two 16384-point transforms,
+// as the vector kernel does, writes every second channel: 16 384 channels of 12
+// stations 1332 us a call against 1124.)
+//
 // Bound by vector issue, at the clock that the chip holds (1.75-1.9 GHz here,
 // 1.93-2.0 in the vector kernel): 38 VALU instructions per station-sample at
 // N = 2048 (vector kernel: 44 dual-pol, 58 single-pol), LDS cycles 0.36x.
 // Whole calls of 8 x 4 inputs, 2^24 samples each: N = 512 dual-pol 1.48 ->
-// 1.03 ms, 2048 1.29 -> 1.05, 8192 1.50 -> 1.24, 16384 1.69 -> 1.28; the ten-station
+// 1.03 ms, 2048 1.29 -> 1.05, 8192 1.50 -> 1.24, 16384 1.69 -> 1.23,
+// 32768 2.00 -> 1.32; the ten-station
 // 4 s scan (N = 2048): F 28.5 -> 26.6 ms.  Its spectra are 2-4e-7 of their RMS
 // from the oracle's (vector kernel: 0.5-2e-6).
 #include <atomic>
@@ -58,16 +65,21 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 // Shape of an N-point frame's transform.
 template <int N>
 struct MGeom {
-  static constexpr int T = N / 16;                          // columns of a frame
+  // first radix: 16, or 32 at N = 32768, half of whose outputs k1 a pass (two
+  // passes over the same codes; a pass's 16-channel runs are whole lines)
+  static constexpr int RAD = N > 16384 ? 32 : 16;
+  static constexpr int HH = RAD / 16;                       // passes
+  static constexpr int KG = RAD / 8;                        // MFMA steps over the samples e
+  static constexpr int T = N / RAD;                         // columns of a frame
   static constexpr int CPF = T < 32 ? T : 32;               // ... in one tile
   static constexpr int FPT = 32 / CPF;                      // frames per tile
   static constexpr int J = T / CPF < 4 ? T / CPF : 4;       // tiles of a frame in a wave
   static constexpr int NF = 4 / J;                          // frames per lane
   static constexpr int FPW = FPT * NF;                      // frames per wave
   static constexpr int WPF = T / (CPF * J);                 // waves per frame
-  static constexpr int R = 16 * J;                          // radix of pass 1 with the DFT over j
+  static constexpr int R = RAD * J;                         // radix of pass 1 with the DFT over j
   static constexpr int L = N / R;                           // points left
-  static constexpr int ROWS = WPF > 1 ? 64 : FPW * R;       // LDS rows of a wave (frame)
+  static constexpr int ROWS = WPF > 1 ? 16 * J : FPW * R;       // LDS rows of a wave (frame)
   static constexpr int RS = L + 2;                          // row stride: 8-byte reads, no conflicts
   static constexpr int WAVES = WPF > 4 ? WPF : 4;           // waves per workgroup
   static constexpr int UNITS = WAVES / WPF;                 // waves or groups of WPF, with own rows
@@ -78,8 +90,10 @@ struct MGeom {
   static constexpr int KB = L / KA;
   static constexpr int unit_f = ROWS * RS;                  // floats of a unit's rows
   static constexpr int fd_n = WPF > 1 ? 16 : FPW * (ROWS > 64 ? 8 : 16);   // a wave's bin phasors
-  // LDS: the matrix (4 KB), the units' rows, the waves' phasors
-  static constexpr size_t rows_off = 4096;
+  // LDS: the matrix (4 KB; 8 for radix 32), the units' rows, the waves' phasors
+  static constexpr size_t lo_off = (size_t)KG * 1024;       // its lower terms
+  static constexpr size_t rows_off = 2 * lo_off;
+  static_assert(WAVES >= RAD / 4, "a wave forms four columns of the matrix");
   static constexpr size_t fd_off = rows_off + (size_t)UNITS * unit_f * sizeof(float);
   // WPF > 1: pass-2 twiddles exp(-2 pi i ta kb / L), [ta][kb] (LDS broadcasts: as scalar
   // operands they overflow the SGPRs, whose spills are vector instructions)
@@ -130,16 +144,15 @@ __device__ inline half2 split_f16(float x) {
 
 typedef const __attribute__((address_space(1))) unsigned char* GlobalBytes;
 
-// exp(-2 pi i k / R), k < R / 4
+// exp(-2 pi i j / R), j < 4
 template <int R>
-__device__ inline float2 tw_const(int k) {
-  constexpr float c[16] = {1.f, 0.99518472667219693f, 0.98078528040323043f, 0.95694033573220882f,
-                           0.92387953251128674f, 0.88192126434835505f, 0.83146961230254524f,
-                           0.77301045336273699f, 0.70710678118654757f, 0.63439328416364549f,
-                           0.55557023301960218f, 0.47139673682599764f, 0.38268343236508978f,
-                           0.29028467725446233f, 0.19509032201612828f, 0.098017140329560604f};
-  const int q = k * (64 / R);
-  return make_float2(c[q], q == 0 ? 0.f : -c[16 - q]);
+__device__ inline float2 tw_const(int j) {
+  constexpr float c[7] = {1.f, 0.99879545620517241f, 0.99518472667219693f, 0.98917650996478101f,
+                          0.98078528040323043f, 0.f, 0.95694033573220882f};
+  constexpr float s[7] = {0.f, 0.049067674327418015f, 0.098017140329560604f, 0.14673047445536175f,
+                          0.19509032201612828f, 0.f, 0.29028467725446233f};
+  const int q = j * (128 / R);   // (j < J, which is 1, 2, 4, 4 at R = 16, 32, 64, 128: q <= 6)
+  return make_float2(c[q], -s[q]);
 }
 
 // exp(2 pi i (d - t) / N), |d| <= 1/2, N >= 256: the table's entry for t turned by a small angle
@@ -200,6 +213,7 @@ __device__ __forceinline__ void fmat_task(const DevJob& Jb, const DelayRec* __re
                                           unsigned char* lds, float* rows, float2* fdt,
                                           const float2* __restrict__ tw) {
   using G = MGeom<N>;
+  constexpr int RAD = G::RAD, KG = G::KG;
   constexpr int T = G::T, J = G::J, NF = G::NF, L = G::L, RS = G::RS, R = G::R, WPF = G::WPF;
   constexpr int RPL = WPF > 1 ? 1 : G::ROWS / 64;   // rows per lane after the exchange
   constexpr int NB = WPF > 1 ? 32 / G::KA : 1;      // WPF > 1: last-pass butterflies per lane
@@ -209,67 +223,66 @@ __device__ __forceinline__ void fmat_task(const DevJob& Jb, const DelayRec* __re
   uint32_t one = 0x3C003C00u;          // (1, 1) in FP16, kept in a register: and-or is one instruction
   __asm__ volatile("" : "+v"(one));
 
-  // The lane's samples e = 2 i + h (i < 8) of its four tiles: their codes, packed
-  // per input (tiles 0, 1 and 2, 3; sample i of tile q: bits 8 (q & 1) + 2 (i >> 1)
-  // of half i & 1), and the frames' phasors
-  uint32_t code[kMatInputs][2] = {};
+  // The lane's samples e = 2 i + h of its four tiles: their codes, packed per
+  // input (i < 8: tiles 0, 1 and 2, 3, then i >= 8; sample i of tile q: bits
+  // 8 (q & 1) + 2 (i % 8 >> 1) of half i & 1), and the frames' phasors
+  uint32_t code[kMatInputs][KG] = {};
   float2 W1[NF], K2[NF][J];
   float on[NF];                        // the levels' scale, or 0 for an invalid frame
-  {
+  GlobalBytes wb[NF];                  // the windows' first recording frames
+  uint32_t pb[NF];                     // ... and the lanes' first payload bytes there
+  int sh0[NF];
+  const int spw = Jb.spw_log2, spf = Jb.spf;
+#pragma unroll
+  for (int i = 0; i < NF; ++i) {
+    const int fl = f0 + i * G::FPT + (G::FPT > 1 ? c / G::CPF : 0);
+    DelayRec r;
+    r.valid = 0;
+    r.d = 0.0;
+    r.base = 0;
+    if (fl < nf) r = drec[(size_t)s * nf + fl];
+    on[i] = r.valid ? 1.0f / kScaleA : 0.0f;
+    W1[i] = bin_step<N>(r.d, tp, tw);
+#pragma unroll
+    for (int k = 1; k < J; ++k) K2[i][k] = phasor_c((double)(RAD * k) * ((r.d - (double)tp) / N));
+    // recording frame of the window start and the offset inside it
+    int64_t fm = (int64_t)((double)r.base * (1.0 / (double)spf));
+    int64_t in = r.base - fm * spf;
+    if (in < 0) {
+      in += spf;
+      --fm;
+    } else if (in >= spf) {
+      in -= spf;
+      ++fm;
+    }
+    wb[i] = (GlobalBytes)(Jb.st[s].words + fm * kFrameWords + kHeaderWords);
+    const int ip = (int)in + tp + T * h;
+    pb[i] = ((uint32_t)ip >> spw) * 4;
+    sh0[i] = 2 * (ip & ((1 << spw) - 1)) * Jb.C;
+  }
+  const int n_in = (sb_hi - sb_lo) * P;
+#pragma unroll
+  for (int eb = 0; eb < RAD / 16; ++eb) {
     uint32_t wv[4][8];
-    int sh0[NF];
-    const int spw = Jb.spw_log2, spf = Jb.spf;
-    const double inv_spf = 1.0 / (double)spf;
 #pragma unroll
-    for (int i = 0; i < NF; ++i) {
-      const int fl = f0 + i * G::FPT + (G::FPT > 1 ? c / G::CPF : 0);
-      DelayRec r;
-      r.valid = 0;
-      r.d = 0.0;
-      r.base = 0;
-      if (fl < nf) r = drec[(size_t)s * nf + fl];
-      on[i] = r.valid ? 1.0f / kScaleA : 0.0f;
-      sh0[i] = 0;
-      W1[i] = bin_step<N>(r.d, tp, tw);
+    for (int q = 0; q < 4; ++q) {
 #pragma unroll
-      for (int k = 1; k < J; ++k) K2[i][k] = phasor_c((double)(16 * k) * ((r.d - (double)tp) / N));
-      if (r.valid) {
-        // recording frame of the window start and the offset inside it
-        int64_t fm = (int64_t)((double)r.base * inv_spf);
-        int64_t in = r.base - fm * spf;
-        if (in < 0) {
-          in += spf;
-          --fm;
-        } else if (in >= spf) {
-          in -= spf;
-          ++fm;
+      for (int e = 0; e < 8; ++e) wv[q][e] = 0u;
+      if (on[q / J] != 0.f) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          // payload byte of the window (T and L are whole numbers of words), and
+          // 16 header bytes more per recording frame passed: x / 10000 =
+          // floor(x 429497 / 2^32) for multiples of 4 below 2^19
+          const uint32_t b =
+              pb[q / J] + (uint32_t)(((L * (q % J) + 2 * T * (8 * eb + e)) >> spw) * 4);
+          __builtin_assume(b < (1u << 19));
+          const uint32_t k = (uint32_t)(((uint64_t)b * 429497u) >> 32);
+          wv[q][e] =
+              *(const __attribute__((address_space(1))) uint32_t*)(wb[q / J] + (b + 16 * k));
         }
-        const GlobalBytes wb =
-            (GlobalBytes)(Jb.st[s].words + fm * kFrameWords + kHeaderWords);
-        const int ip = (int)in + tp + T * h;
-        const uint32_t pb = ((uint32_t)ip >> spw) * 4;
-        sh0[i] = 2 * (ip & ((1 << spw) - 1)) * Jb.C;
-#pragma unroll
-        for (int j = 0; j < J; ++j)
-#pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            // payload byte of the window (T and L are whole numbers of words), and
-            // 16 header bytes more per recording frame passed: x / 10000 =
-            // floor(x 429497 / 2^32) for multiples of 4 below 2^19
-            const uint32_t b = pb + (uint32_t)(((L * j + 2 * T * e) >> spw) * 4);
-            __builtin_assume(b < (1u << 19));
-            const uint32_t q = (uint32_t)(((uint64_t)b * 429497u) >> 32);
-            wv[i * J + j][e] =
-                *(const __attribute__((address_space(1))) uint32_t*)(wb + (b + 16 * q));
-          }
-      } else {
-#pragma unroll
-        for (int j = 0; j < J; ++j)
-#pragma unroll
-          for (int e = 0; e < 8; ++e) wv[i * J + j][e] = 0u;
       }
     }
-    const int n_in = (sb_hi - sb_lo) * P;
 #pragma unroll
     for (int k = 0; k < kMatInputs; ++k)
       if (k < n_in) {
@@ -278,8 +291,8 @@ __device__ __forceinline__ void fmat_task(const DevJob& Jb, const DelayRec* __re
         for (int m = 0; m < 32; ++m) {
           // two bits in at the top: 16 times, so the first ends at the bottom
           const int q = 2 * (m >> 4) + ((m >> 2) & 1), e = 2 * (m & 3) + ((m >> 3) & 1);
-          code[k][m >> 4] = __builtin_amdgcn_alignbit(wv[q][e] >> (sh0[q / J] + map2),
-                                                      code[k][m >> 4], 2);
+          uint32_t& cw = code[k][2 * eb + (m >> 4)];
+          cw = __builtin_amdgcn_alignbit(wv[q][e] >> (sh0[q / J] + map2), cw, 2);
         }
       }
   }
@@ -301,288 +314,293 @@ __device__ __forceinline__ void fmat_task(const DevJob& Jb, const DelayRec* __re
 #pragma unroll 1
   for (int sb = sb_lo; sb < sb_hi; ++sb) {
     const PhaseRec* ph = prec + ((size_t)s * n_sb + sb) * nf;
-    __syncthreads();   // the previous subband's matrix has been read
-    if (wave < 4) {
-      // the matrix: wave p forms the columns e = 2 i + h of i = 2 p, 2 p + 1
-      const PhaseRec pa = ph[fg];
-      const double phi1 =
-          G::FPG > 1 ? 0.5 * (pa.phi1 + ph[min(fg + G::FPG - 1, nf - 1)].phi1) : pa.phi1;
-      double a1 = (double)T * (phi1 + pa.phi2 * (double)T);
-      a1 -= rint(a1);
-      const double a2 = pa.phi2 * (double)T * (double)T;
-      // matrix row of this lane: register i of the product holds rows 8 (i / 4) +
-      // 4 h + i % 4, which are given k1 = 8 h + i / 2 and re / im = i % 2
-      const int row_k1 = 8 * ((c >> 2) & 1) + 2 * (c >> 3) + ((c >> 1) & 1);
-      const double row_im = (c & 1) ? 0.25 : 0.0;    // sin x = cos(x - 1/4 turn)
-      half4 hi, lo;                                  // upper code bit of both, lower of both
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const int e = 2 * (2 * wave + i) + h;
-        const double ee = (double)(e - 8);
-        const double off = (double)((e * row_k1) & 15) * 0.0625 + row_im;
-        const float a = __builtin_amdgcn_cosf(frac_c(fma(ee, fma(ee, a2, a1), -off)));
-        const half2 x = split_f16(a * kScaleX), y = split_f16(a * kScaleY);
-        hi[i] = x[0];
-        hi[i + 2] = y[0];
-        lo[i] = x[1];
-        lo[i + 2] = y[1];
-      }
-      unsigned char* o = lds + (wave >> 1) * 1024 + lane * 16 + (wave & 1) * 8;
-      *reinterpret_cast<half4*>(o) = hi;
-      *reinterpret_cast<half4*>(o + 2048) = lo;
-    }
-    float2 z[NF], S[NF];
-#pragma unroll
-    for (int i = 0; i < NF; ++i) {
-      const int fl = min(f0 + i * G::FPT + (G::FPT > 1 ? c / G::CPF : 0), nf - 1);
-      const PhaseRec pr = ph[fl];
-      const double x = (double)tp;
-      const double g8 = (double)(8 * h) * ((drec[(size_t)s * nf + fl].d - x) / N);
-      z[i] = phasor_c(fma(fma(pr.phi2, x, pr.phi1), x, pr.phi0) + g8);
-      z[i].x *= on[i];
-      z[i].y *= on[i];
-      // step of j: t grows by L, for k1 = 8 h
-      if constexpr (J > 1)
-        S[i] = phasor_c((double)L * (pr.phi1 + 4.0 * pr.phi2 * (double)L) - (double)(8 * h) / R);
-    }
-    __syncthreads();
 #pragma unroll 1
-    for (int p = 0; p < P; ++p) {
-      const int k_in = (sb - sb_lo) * P + p;
-      uint32_t cd[2] = {code[0][0], code[0][1]};
+    for (int hh = 0; hh < G::HH; ++hh) {
+      __syncthreads();   // the previous matrix has been read
+      if (wave < RAD / 4) {
+        // the matrix: wave p forms the columns e = 2 i + h of i = 2 p, 2 p + 1
+        const PhaseRec pa = ph[fg];
+        const double phi1 =
+            G::FPG > 1 ? 0.5 * (pa.phi1 + ph[min(fg + G::FPG - 1, nf - 1)].phi1) : pa.phi1;
+        double a1 = (double)T * (phi1 + pa.phi2 * (double)T);
+        a1 -= rint(a1);
+        const double a2 = pa.phi2 * (double)T * (double)T;
+        // matrix row of this lane: register i of the product holds rows 8 (i / 4) +
+        // 4 h + i % 4, which are given k1 = 8 h + i / 2 and re / im = i % 2
+        const int row_k1 = 16 * hh + 8 * ((c >> 2) & 1) + 2 * (c >> 3) + ((c >> 1) & 1);
+        const double row_im = (c & 1) ? 0.25 : 0.0;    // sin x = cos(x - 1/4 turn)
+        half4 hi, lo;                                  // upper code bit of both, lower of both
 #pragma unroll
-      for (int k = 1; k < kMatInputs; ++k) {
-        cd[0] = k_in == k ? code[k][0] : cd[0];
-        cd[1] = k_in == k ? code[k][1] : cd[1];
+        for (int i = 0; i < 2; ++i) {
+          const int e = 2 * (2 * wave + i) + h;
+          const double ee = (double)(e - RAD / 2);
+          const double off = (double)((e * row_k1) & (RAD - 1)) * (1.0 / RAD) + row_im;
+          const float a = __builtin_amdgcn_cosf(frac_c(fma(ee, fma(ee, a2, a1), -off)));
+          const half2 x = split_f16(a * kScaleX), y = split_f16(a * kScaleY);
+          hi[i] = x[0];
+          hi[i + 2] = y[0];
+          lo[i] = x[1];
+          lo[i + 2] = y[1];
+        }
+        unsigned char* o = lds + (wave >> 1) * 1024 + lane * 16 + (wave & 1) * 8;
+        *reinterpret_cast<half4*>(o) = hi;
+        *reinterpret_cast<half4*>(o + G::lo_off) = lo;
       }
-      float2 v[4][8];
+      float2 z[NF], S[NF];
 #pragma unroll
       for (int i = 0; i < NF; ++i) {
-        float2 zj = z[i];
-#pragma unroll
-        for (int j = 0; j < J; ++j) {
-          f32x16 acc = {};
-#pragma unroll
-          for (int g = 0; g < 2; ++g) {
-            uint4 b;
-            {
-              const uint32_t cw = cd[(i * J + j) >> 1];
-              const int pos = 8 * ((i * J + j) & 1) + 4 * g;
-              b.x = code_signs(cw << (14 - pos), one);
-              b.y = code_signs(cw << (15 - pos), one);
-              b.z = code_signs(pos == 12 ? cw : cw << (12 - pos), one);
-              b.w = code_signs(cw << (13 - pos), one);
-            }
-            const half8 B = __builtin_bit_cast(half8, b);
-            const half8* am = reinterpret_cast<const half8*>(lds) + g * 64 + lane;
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(am[128], B, acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(am[0], B, acc, 0, 0, 0);
-          }
-          // P[k] = zj Wj^k
-          float2 Wa = W1[i];
-          __asm__ volatile("" : "+v"(Wa.x), "+v"(Wa.y), "+v"(zj.x), "+v"(zj.y));   // (per tile)
-          if (j > 0) Wa = cmul(Wa, tw_const<R>(j));
-          const float2 Wb = cmul(Wa, Wa);
-          float2 pa = zj, pb = cmul(zj, Wa);
-#pragma unroll
-          for (int k = 0; k < 8; k += 2) {
-            v[i * J + j][k] = cmul(make_float2(acc[2 * k], acc[2 * k + 1]), pa);
-            v[i * J + j][k + 1] = cmul(make_float2(acc[2 * k + 2], acc[2 * k + 3]), pb);
-            if (k < 6) {
-              pa = cmul(pa, Wb);
-              pb = cmul(pb, Wb);
-            }
-          }
-          if (j + 1 < J) zj = cmul(zj, S[i]);
-          __builtin_amdgcn_sched_barrier(0);   // one tile's operands in registers at a time
-        }
-        // DFT over j and its twiddles; row (frame, k1 + 16 k2), column t'
-        if constexpr (J > 1) {
-#pragma unroll
-          for (int k = 0; k < 8; ++k) {
-            float2 u[J];
-#pragma unroll
-            for (int j = 0; j < J; ++j) u[j] = v[i * J + j][k];
-            Dft<J>::run(u);
-#pragma unroll
-            for (int j = 0; j < J; ++j) v[i * J + j][k] = j == 0 ? u[0] : cmul(u[j], K2[i][j]);
-          }
-        }
+        const int fl = min(f0 + i * G::FPT + (G::FPT > 1 ? c / G::CPF : 0), nf - 1);
+        const PhaseRec pr = ph[fl];
+        const double x = (double)tp, d = drec[(size_t)s * nf + fl].d;
+        const double k0 = (double)(16 * hh + 8 * h);   // k1 of the lane's first row
+        z[i] = phasor_c(fma(fma(pr.phi2, x, pr.phi1), x, pr.phi0) + k0 * ((d - x) / N));
+        z[i].x *= on[i];
+        z[i].y *= on[i];
+        // step of j: t grows by L, for k1 = k0
+        if constexpr (J > 1)
+          S[i] = phasor_c((double)L * (pr.phi1 + 4.0 * pr.phi2 * (double)L) - k0 / R);
       }
-      const int m_in = s * P + p;
-      // exchanges: rows of real, then of imaginary parts (half the LDS of complex rows)
-      float* o = rows + ((G::FPT > 1 ? c / G::CPF : 0) * R + 8 * h) * RS + tp;
-      constexpr int IS = G::FPT * R * RS;     // a tile's (frame's) rows
-      auto put = [&](auto part) {
+      __syncthreads();
+#pragma unroll 1
+      for (int p = 0; p < P; ++p) {
+        const int k_in = (sb - sb_lo) * P + p;
+        uint32_t cd[KG];
 #pragma unroll
-        for (int i = 0; i < NF; ++i)
+        for (int i = 0; i < KG; ++i) {
+          cd[i] = code[0][i];
 #pragma unroll
-          for (int j = 0; j < J; ++j)
+          for (int k = 1; k < kMatInputs; ++k) cd[i] = k_in == k ? code[k][i] : cd[i];
+        }
+        float2 v[4][8];
 #pragma unroll
-            for (int k = 0; k < 8; ++k) o[i * IS + (k + 16 * j) * RS] = part(v[i * J + j][k]);
-      };
-      auto re = [](float2 x) { return x.x; };
-      auto im = [](float2 x) { return x.y; };
-      if constexpr (WPF == 1) {
-        float xr[RPL][L];
-        put(re);
-        wave_sync();
+        for (int i = 0; i < NF; ++i) {
+          float2 zj = z[i];
 #pragma unroll
-        for (int q = 0; q < RPL; ++q)
+          for (int j = 0; j < J; ++j) {
+            f32x16 acc = {};
 #pragma unroll
-          for (int i = 0; i < L / 2; ++i) {
-            const float2 y = reinterpret_cast<const float2*>(rows + (lane + 64 * q) * RS)[i];
-            xr[q][2 * i] = y.x;
-            xr[q][2 * i + 1] = y.y;
+            for (int g = 0; g < KG; ++g) {
+              uint4 b;
+              {
+                const uint32_t cw = cd[2 * (g >> 1) + ((i * J + j) >> 1)];
+                const int pos = 8 * ((i * J + j) & 1) + 4 * (g & 1);
+                b.x = code_signs(cw << (14 - pos), one);
+                b.y = code_signs(cw << (15 - pos), one);
+                b.z = code_signs(pos == 12 ? cw : cw << (12 - pos), one);
+                b.w = code_signs(cw << (13 - pos), one);
+              }
+              const half8 B = __builtin_bit_cast(half8, b);
+              const half8* am = reinterpret_cast<const half8*>(lds) + g * 64 + lane;
+              acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(am[64 * KG], B, acc, 0, 0, 0);
+              acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(am[0], B, acc, 0, 0, 0);
+            }
+            // P[k] = zj Wj^k
+            float2 Wa = W1[i];
+            __asm__ volatile("" : "+v"(Wa.x), "+v"(Wa.y), "+v"(zj.x), "+v"(zj.y));   // (per tile)
+            if (j > 0) Wa = cmul(Wa, tw_const<R>(j));
+            const float2 Wb = cmul(Wa, Wa);
+            float2 pa = zj, pb = cmul(zj, Wa);
+#pragma unroll
+            for (int k = 0; k < 8; k += 2) {
+              v[i * J + j][k] = cmul(make_float2(acc[2 * k], acc[2 * k + 1]), pa);
+              v[i * J + j][k + 1] = cmul(make_float2(acc[2 * k + 2], acc[2 * k + 3]), pb);
+              if (k < 6) {
+                pa = cmul(pa, Wb);
+                pb = cmul(pb, Wb);
+              }
+            }
+            if (j + 1 < J) zj = cmul(zj, S[i]);
+            __builtin_amdgcn_sched_barrier(0);   // one tile's operands in registers at a time
           }
-        wave_sync();
-        put(im);
-        wave_sync();
+          // DFT over j and its twiddles; row (frame, k1 + 16 k2), column t'
+          if constexpr (J > 1) {
 #pragma unroll
-        for (int q = 0; q < RPL; ++q) {
-          const int rho = lane + 64 * q;
-          const float2* x = reinterpret_cast<const float2*>(rows + rho * RS);
-          float2 a[16], b[16];
-          constexpr int K = 16 / RPL;     // kept outputs of the row
+            for (int k = 0; k < 8; ++k) {
+              float2 u[J];
 #pragma unroll
-          for (int i = 0; i < L / 2; ++i) {
-            const float2 y = x[i];
-            if constexpr (L == 32) {
-              a[i] = make_float2(xr[q][2 * i], y.x);
-              b[i] = make_float2(xr[q][2 * i + 1], y.y);
-            } else {
-              a[2 * i] = make_float2(xr[q][2 * i], y.x);
-              a[2 * i + 1] = make_float2(xr[q][2 * i + 1], y.y);
+              for (int j = 0; j < J; ++j) u[j] = v[i * J + j][k];
+              Dft<J>::run(u);
+#pragma unroll
+              for (int j = 0; j < J; ++j) v[i * J + j][k] = j == 0 ? u[0] : cmul(u[j], K2[i][j]);
             }
           }
-          if constexpr (L == 32) {
-            dft32_half(a, b);
-          } else {
-            pin(a);
-            Dft<16>::run(a);
-            pin(a);
-          }
-          const int fl = f0 + rho / R, kap = rho & (R - 1);
-          const float2* fdl = fdt + rho / R * K;
-          if (fl < nf) {
-            // bin kap + R m (low precision: channel-blocked, lp_index)
-            const size_t row = OUT == kOutF32 ? ((size_t)(sb * nf + fl) * M + m_in) * n_chan + kap
-                                              : (size_t)(sb * nf + fl) * M * n_chan +
-                                                    (m_in + (kap >> 4) * M) * 16 + (kap & 15);
-            uint2 ex[2];
-            if constexpr (OUT != kOutF32) {
-              // bin kap + R m: exponent byte m / (N / 16 / R) of the word at its remainder
-              const uint2* exw = reinterpret_cast<const uint2*>(
-                  scale_exp + ((size_t)sb * M + m_in) * n_chan);
-              ex[0] = exw[kap];
-              ex[1] = L == 32 ? exw[kap + R] : ex[0];
-            }
+        }
+        const int m_in = s * P + p;
+        // exchanges: rows of real, then of imaginary parts (half the LDS of complex rows)
+        float* o = rows + ((G::FPT > 1 ? c / G::CPF : 0) * R + 8 * h) * RS + tp;
+        constexpr int IS = G::FPT * R * RS;     // a tile's (frame's) rows
+        auto put = [&](auto part) {
 #pragma unroll
-            for (int m = 0; m < K; ++m) {
-              const float2 y = cmul(a[m], fdl[m]);
-              if constexpr (OUT == kOutF32) {
-                put_spec<OUT>(spec, row + R * m, y, 0);
+          for (int i = 0; i < NF; ++i)
+#pragma unroll
+            for (int j = 0; j < J; ++j)
+#pragma unroll
+              for (int k = 0; k < 8; ++k) o[i * IS + (k + 16 * j) * RS] = part(v[i * J + j][k]);
+        };
+        auto re = [](float2 x) { return x.x; };
+        auto im = [](float2 x) { return x.y; };
+        if constexpr (WPF == 1) {
+          float xr[RPL][L];
+          put(re);
+          wave_sync();
+#pragma unroll
+          for (int q = 0; q < RPL; ++q)
+#pragma unroll
+            for (int i = 0; i < L / 2; ++i) {
+              const float2 y = reinterpret_cast<const float2*>(rows + (lane + 64 * q) * RS)[i];
+              xr[q][2 * i] = y.x;
+              xr[q][2 * i + 1] = y.y;
+            }
+          wave_sync();
+          put(im);
+          wave_sync();
+#pragma unroll
+          for (int q = 0; q < RPL; ++q) {
+            const int rho = lane + 64 * q;
+            const float2* x = reinterpret_cast<const float2*>(rows + rho * RS);
+            float2 a[16], b[16];
+            constexpr int K = 16 / RPL;     // kept outputs of the row
+#pragma unroll
+            for (int i = 0; i < L / 2; ++i) {
+              const float2 y = x[i];
+              if constexpr (L == 32) {
+                a[i] = make_float2(xr[q][2 * i], y.x);
+                b[i] = make_float2(xr[q][2 * i + 1], y.y);
               } else {
-                const int byte = L == 32 ? m >> 1 : m;
-                const uint2 e2 = ex[L == 32 ? m & 1 : 0];
-                const uint32_t ew = byte < 4 ? e2.x : e2.y;
-                put_spec<OUT>(spec, row + R * M * m, y, (int)(ew << (24 - 8 * (byte & 3))) >> 24);
+                a[2 * i] = make_float2(xr[q][2 * i], y.x);
+                a[2 * i + 1] = make_float2(xr[q][2 * i + 1], y.y);
+              }
+            }
+            if constexpr (L == 32) {
+              dft32_half(a, b);
+            } else {
+              pin(a);
+              Dft<16>::run(a);
+              pin(a);
+            }
+            const int fl = f0 + rho / R, kap = rho & (R - 1);
+            const float2* fdl = fdt + rho / R * K;
+            if (fl < nf) {
+              // bin kap + R m (low precision: channel-blocked, lp_index)
+              const size_t row = OUT == kOutF32 ? ((size_t)(sb * nf + fl) * M + m_in) * n_chan + kap
+                                                : (size_t)(sb * nf + fl) * M * n_chan +
+                                                      (m_in + (kap >> 4) * M) * 16 + (kap & 15);
+              uint2 ex[2];
+              if constexpr (OUT != kOutF32) {
+                // bin kap + R m: exponent byte m / (N / 16 / R) of the word at its remainder
+                const uint2* exw = reinterpret_cast<const uint2*>(
+                    scale_exp + ((size_t)sb * M + m_in) * n_chan);
+                ex[0] = exw[kap];
+                ex[1] = L == 32 ? exw[kap + R] : ex[0];
+              }
+#pragma unroll
+              for (int m = 0; m < K; ++m) {
+                const float2 y = cmul(a[m], fdl[m]);
+                if constexpr (OUT == kOutF32) {
+                  put_spec<OUT>(spec, row + R * m, y, 0);
+                } else {
+                  const int byte = L == 32 ? m >> 1 : m;
+                  const uint2 e2 = ex[L == 32 ? m & 1 : 0];
+                  const uint32_t ew = byte < 4 ? e2.x : e2.y;
+                  put_spec<OUT>(spec, row + R * M * m, y, (int)(ew << (24 - 8 * (byte & 3))) >> 24);
+                }
               }
             }
           }
-        }
-        wave_sync();   // the next input writes the rows
-      } else {
-        constexpr int KA = G::KA, KB = G::KB, TAW = KA / WPF;
-        const float2* tab = reinterpret_cast<const float2*>(lds + G::tw_off) + TAW * w * KB;
-        // lane = row k1 + 16 k2; this wave's columns ta = TAW w + a, all tb
-        float2 y2[TAW][KB];
-        const float2* x = reinterpret_cast<const float2*>(rows + lane * RS + TAW * w);
-        put(re);   // (the rows are free: every wave is past its last reads)
-        __syncthreads();
+          wave_sync();   // the next input writes the rows
+        } else {
+          constexpr int KA = G::KA, KB = G::KB, TAW = KA / WPF;
+          const float2* tab = reinterpret_cast<const float2*>(lds + G::tw_off) + TAW * w * KB;
+          // lane = row k1 + 16 k2; this wave's columns ta = TAW w + a, all tb
+          float2 y2[TAW][KB];
+          const float2* x = reinterpret_cast<const float2*>(rows + lane * RS + TAW * w);
+          put(re);   // (the rows are free: every wave is past its last reads)
+          __syncthreads();
 #pragma unroll
-        for (int b = 0; b < KB; ++b)
+          for (int b = 0; b < KB; ++b)
 #pragma unroll
-          for (int a = 0; a < TAW; a += 2) {
-            const float2 y = x[(KA * b + a) / 2];
-            y2[a][b].x = y.x;
-            y2[a + 1][b].x = y.y;
+            for (int a = 0; a < TAW; a += 2) {
+              const float2 y = x[(KA * b + a) / 2];
+              y2[a][b].x = y.x;
+              y2[a + 1][b].x = y.y;
+            }
+          __syncthreads();
+          put(im);
+          __syncthreads();
+#pragma unroll
+          for (int b = 0; b < KB; ++b)
+#pragma unroll
+            for (int a = 0; a < TAW; a += 2) {
+              const float2 y = x[(KA * b + a) / 2];
+              y2[a][b].y = y.x;
+              y2[a + 1][b].y = y.y;
+            }
+#pragma unroll
+          for (int a = 0; a < TAW; ++a) {
+            pin(y2[a]);
+            Dft<KB>::run(y2[a]);
+            pin(y2[a]);
+#pragma unroll
+            for (int b = 1; b < KB; ++b) y2[a][b] = cmul(y2[a][b], tab[a * KB + b]);
           }
-        __syncthreads();
-        put(im);
-        __syncthreads();
+          // second exchange [ta][kb][row]: this wave's kb, all ta
+          float* o2 = rows + TAW * w * KB * 64 + lane;
+          const float* x2 = rows + lane;
+          float2 u[NB][KA];
+          __syncthreads();
 #pragma unroll
-        for (int b = 0; b < KB; ++b)
+          for (int a = 0; a < TAW; ++a)
 #pragma unroll
-          for (int a = 0; a < TAW; a += 2) {
-            const float2 y = x[(KA * b + a) / 2];
-            y2[a][b].y = y.x;
-            y2[a + 1][b].y = y.y;
-          }
+            for (int b = 0; b < KB; ++b) o2[(a * KB + b) * 64] = y2[a][b].x;
+          __syncthreads();
 #pragma unroll
-        for (int a = 0; a < TAW; ++a) {
-          pin(y2[a]);
-          Dft<KB>::run(y2[a]);
-          pin(y2[a]);
+          for (int i = 0; i < NB; ++i)
 #pragma unroll
-          for (int b = 1; b < KB; ++b) y2[a][b] = cmul(y2[a][b], tab[a * KB + b]);
-        }
-        // second exchange [ta][kb][row]: this wave's kb, all ta
-        float* o2 = rows + TAW * w * KB * 64 + lane;
-        const float* x2 = rows + lane;
-        float2 u[NB][KA];
-        __syncthreads();
+            for (int a = 0; a < KA; ++a)
+              u[i][a].x = x2[(a * KB + 2 * w + (i & 1) + (KB / 2) * (i >> 1)) * 64];
+          __syncthreads();
 #pragma unroll
-        for (int a = 0; a < TAW; ++a)
+          for (int a = 0; a < TAW; ++a)
 #pragma unroll
-          for (int b = 0; b < KB; ++b) o2[(a * KB + b) * 64] = y2[a][b].x;
-        __syncthreads();
+            for (int b = 0; b < KB; ++b) o2[(a * KB + b) * 64] = y2[a][b].y;
+          __syncthreads();
 #pragma unroll
-        for (int i = 0; i < NB; ++i)
+          for (int i = 0; i < NB; ++i)
 #pragma unroll
-          for (int a = 0; a < KA; ++a)
-            u[i][a].x = x2[(a * KB + 2 * w + (i & 1) + (KB / 2) * (i >> 1)) * 64];
-        __syncthreads();
+            for (int a = 0; a < KA; ++a)
+              u[i][a].y = x2[(a * KB + 2 * w + (i & 1) + (KB / 2) * (i >> 1)) * 64];
+          __syncthreads();   // the next input writes the rows
+          if (f0 < nf) {
+            const size_t row = OUT == kOutF32 ? ((size_t)(sb * nf + f0) * M + m_in) * n_chan + 16 * hh +
+                                                    RAD * (lane >> 4) + (lane & 15)
+                                              : (size_t)(sb * nf + f0) * M * n_chan +
+                                                    (m_in + (lane >> 4) * M) * 16 + (lane & 15);
+            uint2 ex[2];
+            if constexpr (OUT != kOutF32) {
+              // bin lane + 64 kr, kr = kb + KB ka: byte kr / (N / 1024) of the word at the remainder
+              const uint2* exw =
+                  reinterpret_cast<const uint2*>(scale_exp + ((size_t)sb * M + m_in) * n_chan);
 #pragma unroll
-        for (int a = 0; a < TAW; ++a)
+              for (int i = 0; i < 2; ++i) ex[i] = exw[lane + 64 * ((2 * w + i) & (N / 1024 - 1))];
+            }
 #pragma unroll
-          for (int b = 0; b < KB; ++b) o2[(a * KB + b) * 64] = y2[a][b].y;
-        __syncthreads();
+            for (int i = 0; i < NB; ++i) {
+              const int kb = 2 * w + (i & 1) + (KB / 2) * (i >> 1);
+              pin(u[i]);
+              Dft<KA>::run(u[i]);
+              pin(u[i]);
 #pragma unroll
-        for (int i = 0; i < NB; ++i)
-#pragma unroll
-          for (int a = 0; a < KA; ++a)
-            u[i][a].y = x2[(a * KB + 2 * w + (i & 1) + (KB / 2) * (i >> 1)) * 64];
-        __syncthreads();   // the next input writes the rows
-        if (f0 < nf) {
-          const size_t row = OUT == kOutF32 ? ((size_t)(sb * nf + f0) * M + m_in) * n_chan + lane
-                                            : (size_t)(sb * nf + f0) * M * n_chan +
-                                                  (m_in + (lane >> 4) * M) * 16 + (lane & 15);
-          uint2 ex[2];
-          if constexpr (OUT != kOutF32) {
-            // bin lane + 64 kr, kr = kb + KB ka: byte kr / (N / 1024) of the word at the remainder
-            const uint2* exw =
-                reinterpret_cast<const uint2*>(scale_exp + ((size_t)sb * M + m_in) * n_chan);
-#pragma unroll
-            for (int i = 0; i < 2; ++i) ex[i] = exw[lane + 64 * ((2 * w + i) & (N / 1024 - 1))];
-          }
-#pragma unroll
-          for (int i = 0; i < NB; ++i) {
-            const int kb = 2 * w + (i & 1) + (KB / 2) * (i >> 1);
-            pin(u[i]);
-            Dft<KA>::run(u[i]);
-            pin(u[i]);
-#pragma unroll
-            for (int a = 0; a < KA / 2; ++a) {
-              const float2 y = cmul(u[i][a], fdt[i * (KA / 2) + a]);
-              const int kr = kb + KB * a;
-              if constexpr (OUT == kOutF32) {
-                put_spec<OUT>(spec, row + 64 * kr, y, 0);
-              } else {
-                const int byte = kr / (N / 1024);
-                const uint32_t ew = byte < 4 ? ex[i & 1].x : ex[i & 1].y;
-                put_spec<OUT>(spec, row + 64 * M * kr, y,
-                              (int)(ew << (24 - 8 * (byte & 3))) >> 24);
+              for (int a = 0; a < KA / 2; ++a) {
+                const float2 y = cmul(u[i][a], fdt[i * (KA / 2) + a]);
+                const int kr = kb + KB * a;
+                if constexpr (OUT == kOutF32) {
+                  put_spec<OUT>(spec, row + R * kr, y, 0);
+                } else {
+                  const int byte = kr / (N / 1024);
+                  const uint32_t ew = byte < 4 ? ex[i & 1].x : ex[i & 1].y;
+                  put_spec<OUT>(spec, row + 64 * M * kr, y,
+                                (int)(ew << (24 - 8 * (byte & 3))) >> 24);
+                }
               }
             }
           }
@@ -710,12 +728,11 @@ template <int N>
 hipError_t launch_fmat_n(const DevJob* job, int n_stations, int n_subbands, int n_pols,
                          const DelayRec* drec, const PhaseRec* prec, const float2* tw, void* spec,
                          const int8_t* scale_exp, int nf, int out, hipStream_t s) {
-  if (out == kOutF16)
-    return launch_fmat_no<N, kOutF16>(job, n_stations, n_subbands, n_pols, drec, prec, tw, spec, scale_exp,
-                                      nf, s);
-  if (out == kOutF8)
-    return launch_fmat_no<N, kOutF8>(job, n_stations, n_subbands, n_pols, drec, prec, tw, spec, scale_exp,
-                                     nf, s);
+  if constexpr (N > 256)   // (matrix_out_ok)
+    if (out == kOutF16)
+      return launch_fmat_no<N, kOutF16>(job, n_stations, n_subbands, n_pols, drec, prec, tw, spec,
+                                        scale_exp, nf, s);
+  if (out != kOutF32) return hipErrorInvalidValue;
   return launch_fmat_no<N, kOutF32>(job, n_stations, n_subbands, n_pols, drec, prec, tw, spec, scale_exp,
                                     nf, s);
 }
@@ -780,6 +797,10 @@ hipError_t launch_fmat(int N, const DevJob* job, int n_stations, int n_subbands,
     XC_MCASE(256) XC_MCASE(512) XC_MCASE(1024) XC_MCASE(2048) XC_MCASE(4096) XC_MCASE(8192)
     XC_MCASE(16384)
 #undef XC_MCASE
+    case 32768:
+      if (out != kOutF32) return hipErrorInvalidValue;
+      return launch_fmat_no<32768, kOutF32>(job, n_stations, n_subbands, n_pols, drec, prec, tw,
+                                            spec, nullptr, nf, s);
     default: return hipErrorInvalidValue;
   }
 }

@@ -116,7 +116,7 @@ constexpr int kLeanGroup = 4;   // inputs per lean task
 // kFstageMatrix: the first pass on the matrix cores (k_fmat.hip), for jobs that
 // pass fstage_matrix_ok.
 constexpr int kFstageMatrix = 9;
-constexpr int kMaxMatrixN = 16384;
+constexpr int kMaxMatrixN = 32768;
 // The F-stage variant a job runs.  `mat` (the job passes fstage_matrix_ok, and
 // low-precision spectra matrix_out_ok): the matrix-core kernel, except where
 // variant 5 or 7 is tuned, which round their own way.
@@ -131,9 +131,10 @@ constexpr int kMaxMatrixN = 16384;
 // spectra land on the neighbouring FP16 or e4m3 value (2e-3 of the FP16 ones).
 // Over 1024 frames of FP16 that averages to below 5e-6 of the products; e4m3's
 // coarser steps would need some 16 000 and keep the vector kernel, as does
-// FP16 at 256 points, where its 16-channel runs leave the matrix kernel 3 % behind.
+// FP16 at 256 points, where its 16-channel runs leave the matrix kernel 3 % behind
+// (32768 points: FP32 only).
 inline bool matrix_out_ok(int N, int out, int64_t n_frames) {
-  return out == kOutF32 || (out == kOutF16 && N > 256 && n_frames >= 1024);
+  return out == kOutF32 || (out == kOutF16 && N > 256 && N <= 16384 && n_frames >= 1024);
 }
 inline int fstage_variant(int tuned, bool mat, int n_pols, int n_chan, int out, int64_t n_frames) {
   const int N = 2 * n_chan;
@@ -152,7 +153,7 @@ hipError_t launch_fstage(int N, const DevJob* job, int n_stations, int n_subband
                          const DelayRec* drec, const PhaseRec* prec, const float2* tw,
                          void* spec, const int8_t* scale_exp, int nf, int waves, int out,
                          unsigned* ctr, float2* scratch, hipStream_t s);
-// The F stage on the matrix cores (N <= 16384, any output; the job must pass
+// The F stage on the matrix cores (32768 points: FP32 spectra; the job must pass
 // fstage_matrix_ok): its tasks, each of spt subbands of a station and frame group.
 hipError_t launch_fmat(int N, const DevJob* job, int n_stations, int n_subbands, int n_pols,
                        const DelayRec* drec, const PhaseRec* prec, const float2* tw, void* spec,

@@ -140,7 +140,7 @@ int upload_desc(xc_ctx* c, const xc_setup* s, const xc_station* st, const Layout
 bool any_rate_correct(const xc_setup* s, const xc_station* st);
 // Accumulator slots that the X stage writes for a block of nf frames.
 int slots_used(int nf, int fps_max, int M, int n_chan, int n_subbands);
-// Can the job's F stage run on the matrix cores (N <= 16384, and a fringe phase
+// Can the job's F stage run on the matrix cores (a fringe phase
 // whose curvature inside a frame is small enough for that kernel)?
 bool fstage_matrix_ok(const xc_setup* s, const xc_station* st);
 // Enqueue every kernel of one job (delays .. finalise) on `stream`; with two

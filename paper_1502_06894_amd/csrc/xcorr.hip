@@ -189,9 +189,10 @@ bool fstage_matrix_ok(const xc_setup* s, const xc_station* st) {
   }
   // left out of the phase, in turns: within a frame 2 phi2 (t - T/2) T (e - 8) <=
   // N^2 phi2 / 32 and N^2 phi2 / 800 from the step of j; between the F frames
-  // of a task, which share their middle's slope, 9/16 (F - 1) N^2 phi2
+  // of a task, which share their middle's slope, 9/16 (F - 1) N^2 phi2; at
+  // 32768 points (radix 32, T = N / 32) half of the first, N^2 phi2 / 64
   const int F = fmat_frames_per_task(N);
-  return phi2 * (double)N * (double)N * (0.0325 + 0.5625 * (F - 1)) <= 3e-8;
+  return phi2 * (double)N * (double)N * ((N == 32768 ? 0.016 : 0.0325) + 0.5625 * (F - 1)) <= 3e-8;
 }
 
 Layout layout_of(const xc_setup* s, const xc_station* st, const xc_tuning& tu, bool overlap) {

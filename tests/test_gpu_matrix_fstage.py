@@ -38,7 +38,7 @@ def corr(xc):
     (128, 16, 5, 1, 33), (128, 1, 1, 1, 1), (256, 8, 3, 2, 17), (256, 2, 1, 1, 15),
     (512, 4, 1, 2, 9), (512, 16, 6, 1, 7), (1024, 16, 5, 2, 5), (1024, 1, 1, 1, 3),
     (2048, 2, 2, 1, 3), (2048, 16, 7, 1, 1), (4096, 8, 3, 1, 2), (8192, 4, 1, 2, 2),
-    (8192, 16, 5, 1, 1),
+    (8192, 16, 5, 1, 1), (16384, 8, 3, 2, 3), (16384, 2, 1, 1, 2),
 ])
 def test_spectra(xc, corr, n_chan, C, nsb, P, nf):
     """Spectra of every input, with a bad recording frame in one station and
