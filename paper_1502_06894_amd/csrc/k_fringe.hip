@@ -1,8 +1,9 @@
 // Delay-rate fringe search over stacked sub-integrations (the search behind
 // the paper's first-fringe result, section 2): a zero-padded FFT over the
-// channels of every (sub-integration, subband, baseline) row, then per
-// (subband, baseline) a zero-padded FFT over sub-integrations of every delay
-// column, the windowed peak and its parabolic refinement.
+// channels of every (sub-integration, subband, baseline) row, then per chunk
+// of delay columns of every (subband, baseline) map a zero-padded FFT over
+// sub-integrations and the chunk's windowed peak, then per map the parabolic
+// refinement of its best peak.
 #include <math.h>
 
 #include <atomic>
@@ -13,8 +14,8 @@
 
 namespace xc {
 
-// Delay transform: rows q = (t, sb, bl) of vis [T][n_sb][nbl][n_chan], each
-// zero-padded to D, into F [n_sb][nbl][T][D].  A workgroup runs kDelayIters
+// Delay transform: rows q = (t, map) of vis [T][n_maps][n_chan], each
+// zero-padded to D, into F [n_maps][T][D].  A workgroup runs kDelayIters
 // groups of G rows (T threads a row, as in the F stage's FFT), with the
 // twiddles in LDS tables filled once: the full per-pass tables up to D = 2048,
 // the split ones above (less LDS, more resident workgroups).
@@ -32,10 +33,19 @@ struct RowGeom {
       ((size_t)G * lds_words<D>() + (size_t)tw_entries) * sizeof(float2);
 };
 
-template <int D>
+// A map's best peak while its chunks run: the upper half of the key is |G|^2
+// (its bits order like the value), the lower the complement of the bin index, so
+// the largest key is the largest value, of the smallest index on a tie.  It sits
+// in the map's entry of the result until the refinement writes that.
+__device__ inline unsigned long long* peak_key(xc_fringe_peak* p) {
+  return reinterpret_cast<unsigned long long*>(p);
+}
+
+template <int D, bool HALF>
 __global__ void __launch_bounds__(RowGeom<D>::WG)
     k_fringe_delay(const float2* __restrict__ vis, float2* __restrict__ F,
-                   const float2* __restrict__ tw, int n_sub, int n_sb, int nbl, int n_chan) {
+                   const float2* __restrict__ tw, xc_fringe_peak* __restrict__ peaks, int n_sub,
+                   int n_maps, int n_chan) {
   using Gm = RowGeom<D>;
   constexpr int T = Gm::T, E = Gm::E, G = Gm::G;
   extern __shared__ float2 lds_all[];
@@ -45,30 +55,42 @@ __global__ void __launch_bounds__(RowGeom<D>::WG)
   else
     tw_lds_fill<D>(tab, tw, threadIdx.x, blockDim.x);
   const int g = threadIdx.x / T, t = threadIdx.x % T;
-  const long n_rows = (long)n_sub * n_sb * nbl;
+  const long n_rows = (long)n_sub * n_maps;
+  // no peak found yet
+  for (int m = blockIdx.x * blockDim.x + threadIdx.x; m < n_maps; m += gridDim.x * blockDim.x)
+    *peak_key(peaks + m) = 0ull;
+  // a row's samples n = t + e T; HALF: the upper half are the padding's zeros,
+  // which leaves registers to load the next row while this one is transformed
+  constexpr int EL = HALF ? E / 2 : E;
+  float2 nx[EL];
+  auto load = [&](int it) {
+    const long q = ((long)blockIdx.x * kDelayIters + it) * G + g;
+    const float2* x = vis + q * n_chan;
+#pragma unroll
+    for (int e = 0; e < EL; ++e) {
+      const int n = t + e * T;
+      nx[e] = q < n_rows && n < n_chan ? x[n] : make_float2(0.f, 0.f);
+    }
+  };
+  if constexpr (HALF) load(0);
 #pragma unroll 1
   for (int it = 0; it < kDelayIters; ++it) {
+    if constexpr (!HALF) load(it);
     __syncthreads();   // tables written / the previous group's exchange done
     const long q = ((long)blockIdx.x * kDelayIters + it) * G + g;
-    // the row's indices (rows past the end transform zeros and store nothing)
-    const bool live = q < n_rows;
-    const long qq = live ? q : 0;
-    const int bl = (int)(qq % nbl);
-    const int sb = (int)((qq / nbl) % n_sb);
-    const int ts = (int)(qq / ((long)nbl * n_sb));
-    const float2* x = vis + qq * n_chan;
+    const bool live = q < n_rows;   // (rows past the end transform zeros and store nothing)
     float2 v[E];
 #pragma unroll
-    for (int e = 0; e < E; ++e) {
-      const int n = t + e * T;
-      v[e] = live && n < n_chan ? x[n] : make_float2(0.f, 0.f);
-    }
+    for (int e = 0; e < E; ++e) v[e] = e < EL ? nx[e < EL ? e : 0] : make_float2(0.f, 0.f);
+    if constexpr (HALF)
+      if (it + 1 < kDelayIters) load(it + 1);
     if constexpr (Gm::split)
       fft_forward<D>(v, lds_all + g * lds_words<D>(), TwSplit<D>{tab}, t);
     else
       fft_forward<D>(v, lds_all + g * lds_words<D>(), TwLds<D>{tab}, t);
     if (!live) continue;
-    float2* out = F + (((size_t)sb * nbl + bl) * n_sub + ts) * D;
+    const int m = (int)(q % n_maps), ts = (int)(q / n_maps);
+    float2* out = F + ((size_t)m * n_sub + ts) * D;
     constexpr int B = E / 16;
 #pragma unroll
     for (int b = 0; b < B; ++b)
@@ -77,12 +99,20 @@ __global__ void __launch_bounds__(RowGeom<D>::WG)
   }
 }
 
-// Rate transform, peak and refinement: one workgroup (256 threads) per
+// Rate transform and peak: one workgroup (256 threads) per chunk of columns of a
 // (subband, baseline) map.  Each round takes GC delay columns; a column's
 // R-point transform over sub-integrations (zero-padded from n_sub) runs on
 // TR = R/16 threads of 16 values (the LDS Stockham FFT) for R >= 32, or in one
 // thread's registers for R <= 16.  Thread (tl, c) = threadIdx tl GC + c, so a
 // wave's loads of one sub-integration row are consecutive columns.
+// A whole map per workgroup takes 180 us however few maps there are (R = 128,
+// 2048 delays), and 1680 maps would be 2.2 rounds of the GPU; in chunks, 64 maps
+// of 64 sub-integrations and 1024 channels take 85 us a call instead of 232, 960
+// of 200 sub-integrations (R = 512) 355 instead of 870.  At four waves per SIMD
+// and with a round's columns interleaved in LDS (ColIdx: half of the LDS cycles
+// were bank conflicts) the kernel takes 409 us for 1680 maps (736 before),
+// 4.3 TB/s of F; the delay kernel before it streams at a copy's rate (557 us,
+// 4.8 TB/s).
 constexpr int kFringeThreads = 256;
 
 template <int R>
@@ -91,8 +121,11 @@ struct RateGeom {
   static constexpr int TR = fft ? R / 16 : 1;       // threads per column
   static constexpr int E = fft ? 16 : R;            // values per thread
   static constexpr int GC = kFringeThreads / TR;    // columns per round
+  // up to 256 points the columns of a round lie interleaved in LDS
+  static constexpr bool col = GC >= 16;
+  static constexpr int words = !fft ? 0 : col ? R * GC + (GC < 32 ? R : 0) : GC * lds_words<R>();
   static constexpr size_t lds_bytes =
-      fft ? ((size_t)GC * lds_words<R>() + (size_t)tw_lds_entries<R>()) * sizeof(float2) : 0;
+      fft ? ((size_t)words + (size_t)tw_lds_entries<R>()) * sizeof(float2) : 0;
 };
 
 template <int R>
@@ -109,17 +142,16 @@ __device__ inline bool better(float a, int ia, float b, int ib) {
 }
 
 // G[r, d] by direct summation over sub-integrations (the refinement's
-// neighbours), twiddles exp(-2 pi i m / R) from the global table
+// neighbours), in their order, twiddles exp(-2 pi i m / R) from the global table
 __device__ inline float2 rate_point(const float2* __restrict__ Fm, const float2* __restrict__ tw,
                                     int n_sub, int R, int D, int r, int d) {
   float2 acc = make_float2(0.f, 0.f);
-  int m = 0;
+#pragma unroll 8
   for (int ts = 0; ts < n_sub; ++ts) {
     const float2 f = Fm[(size_t)ts * D + d];
-    const float2 w = tw[(size_t)m * (kTwiddleN / R)];
+    const float2 w = tw[(size_t)((ts * r) & (R - 1)) * (kTwiddleN / R)];
     acc.x = fmaf(f.x, w.x, fmaf(-f.y, w.y, acc.x));
     acc.y = fmaf(f.x, w.y, fmaf(f.y, w.x, acc.y));
-    m = (m + r) & (R - 1);
   }
   return acc;
 }
@@ -129,34 +161,39 @@ __device__ inline float parabola_off(float am, float a0, float ap) {
   return den == 0.f ? 0.f : (am - ap) / (2.f * den);
 }
 
-template <int R>
-__global__ void __launch_bounds__(kFringeThreads)
+template <int R, bool HALF>
+__global__ void __launch_bounds__(kFringeThreads, 4)
     k_fringe_rate(const float2* __restrict__ F, const float2* __restrict__ tw,
                   xc_fringe_peak* __restrict__ peaks, float2* __restrict__ map, int n_sub, int D,
-                  int n_chan, int delay_win, int rate_win, double dnu, double t_int) {
+                  int cols, int delay_win, int rate_win) {
   using Rg = RateGeom<R>;
   constexpr int TR = Rg::TR, E = Rg::E, GC = Rg::GC;
   extern __shared__ float2 sh[];
-  __shared__ float best_v[kFringeThreads];
-  __shared__ int best_i[kFringeThreads];
   const int map_id = blockIdx.x;
   const float2* Fm = F + (size_t)map_id * n_sub * D;
-  float2* tab = sh + GC * (Rg::fft ? lds_words<R>() : 0);
+  float2* tab = sh + Rg::words;
   if constexpr (Rg::fft) tw_lds_fill<R>(tab, tw, threadIdx.x, blockDim.x);
   const int c = threadIdx.x % GC, tl = threadIdx.x / GC;
   float bv = -1.f;
   int bi = 0x7fffffff;
-  auto load = [&](float2 (&v)[E], int d) {
+  // a column's sub-integrations ts = tl + e TR; HALF: the upper half are zeros,
+  // which leaves registers to load the next round while this one is transformed
+  constexpr int EL = HALF ? E / 2 : E;
+  float2 nx[EL];
+  auto load = [&](int d) {
 #pragma unroll
-    for (int e = 0; e < E; ++e) {
+    for (int e = 0; e < EL; ++e) {
       const int ts = tl + e * TR;
-      v[e] = ts < n_sub ? Fm[(size_t)ts * D + d] : make_float2(0.f, 0.f);
+      nx[e] = ts < n_sub ? Fm[(size_t)ts * D + d] : make_float2(0.f, 0.f);
     }
   };
   auto search = [&](float2 (&v)[E], int d) {
     if constexpr (Rg::fft) {
       __syncthreads();   // tables written / the previous round's exchange done
-      fft_forward<R>(v, sh + c * lds_words<R>(), TwLds<R>{tab}, tl);
+      if constexpr (Rg::col)
+        fft_forward<R, ColIdx<GC>>(v, sh + c, TwLds<R>{tab}, tl);
+      else
+        fft_forward<R>(v, sh + c * lds_words<R>(), TwLds<R>{tab}, tl);
     } else {
       small_dft<R>(v);
     }
@@ -166,85 +203,93 @@ __global__ void __launch_bounds__(kFringeThreads)
 #pragma unroll
       for (int j = 0; j < E; ++j) map[((size_t)map_id * R + rate_of(j)) * D + d] = v[j];
     }
-    // the round's largest |G|^2 (first j on ties: the smallest index r D + d),
-    // then one comparison with the thread's best under the tie rule
+    // the round's largest |G|^2; only where it reaches the thread's best so far
+    // (seldom, after a few rounds) its index, the first j on ties: the smallest r D + d
+    float a2[E];
+    const int ds = signed_bin(d, D);
+    const bool d_in = delay_win <= 0 || (ds <= delay_win && ds >= -delay_win);
     float m = -1.f;
-    int mj = 0;
-    if (delay_win <= 0 && rate_win <= 0) {
 #pragma unroll
-      for (int j = 0; j < E; ++j) {
-        const float a2 = v[j].x * v[j].x + v[j].y * v[j].y;
-        if (a2 > m) {
-          m = a2;
-          mj = j;
-        }
-      }
-    } else {
-      const int ds = signed_bin(d, D);
-      const bool d_in = delay_win <= 0 || (ds <= delay_win && ds >= -delay_win);
-#pragma unroll
-      for (int j = 0; j < E; ++j) {
+    for (int j = 0; j < E; ++j) {
+      a2[j] = v[j].x * v[j].x + v[j].y * v[j].y;
+      if (rate_win > 0) {
         const int rs = signed_bin(rate_of(j), R);
-        const bool in = d_in && (rate_win <= 0 || (rs <= rate_win && rs >= -rate_win));
-        const float a2 = v[j].x * v[j].x + v[j].y * v[j].y;
-        if (in && a2 > m) {
-          m = a2;
-          mj = j;
-        }
+        if (rs > rate_win || rs < -rate_win) a2[j] = -1.f;
       }
+      m = fmaxf(m, a2[j]);
     }
-    const int idx = rate_of(mj) * D + d;
-    if (m >= 0.f && better(m, idx, bv, bi)) {
-      bv = m;
-      bi = idx;
+    if (d_in && m >= fmaxf(bv, 0.f)) {
+      int mj = 0;
+#pragma unroll
+      for (int j = E - 1; j >= 0; --j) mj = a2[j] == m ? j : mj;
+      const int idx = rate_of(mj) * D + d;
+      if (better(m, idx, bv, bi)) {
+        bv = m;
+        bi = idx;
+      }
     }
   };
-  // D >= 256 is a multiple of GC (<= 256): every round is full.  Two rounds'
-  // columns are loaded together, so the second's loads overlap the first's
-  // transform.
+  // cols is a multiple of GC and divides D: every round is full
+  const int d_end = ((int)blockIdx.y + 1) * cols;
+  int d = (int)blockIdx.y * cols + c;
+  if constexpr (HALF) load(d);
 #pragma unroll 1
-  for (int d0 = 0; d0 < D; d0 += 2 * GC) {
-    const bool two = d0 + GC < D;
-    float2 v0[E], v1[E];
-    load(v0, d0 + c);
-    if (two) load(v1, d0 + GC + c);
-    search(v0, d0 + c);
-    if (two) search(v1, d0 + GC + c);
+  for (; d < d_end; d += GC) {
+    if constexpr (!HALF) load(d);
+    float2 v[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) v[e] = e < EL ? nx[e < EL ? e : 0] : make_float2(0.f, 0.f);
+    if constexpr (HALF)
+      if (d + GC < d_end) load(d + GC);
+    search(v, d);
   }
-  best_v[threadIdx.x] = bv;
-  best_i[threadIdx.x] = bi;
-  __syncthreads();
-  for (int w = kFringeThreads / 2; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w &&
-        better(best_v[threadIdx.x + w], best_i[threadIdx.x + w], best_v[threadIdx.x],
-               best_i[threadIdx.x])) {
-      best_v[threadIdx.x] = best_v[threadIdx.x + w];
-      best_i[threadIdx.x] = best_i[threadIdx.x + w];
-    }
-    __syncthreads();
+  // (a thread without a candidate: every value outside the window or not a number)
+  unsigned long long key =
+      bv >= 0.f ? (unsigned long long)__float_as_uint(bv) << 32 | (0xffffffffu - (unsigned)bi) : 0ull;
+  for (int w = 32; w > 0; w >>= 1) {
+    const unsigned long long o = __shfl_xor(key, w);
+    key = o > key ? o : key;
   }
-  // the peak value and its four cyclic neighbours, recomputed from memory
-  __shared__ float2 pts[5];
-  const int pi = best_i[0];
-  const int pr = pi / D, pd = pi - pr * D;
-  if (threadIdx.x < 5) {
-    const int k = threadIdx.x;
+  if ((threadIdx.x & 63) == 0 && key) atomicMax(peak_key(peaks + map_id), key);
+}
+
+// The best peak's value and its four cyclic neighbours, recomputed from memory
+// (a thread each), and the parabolic refinement: kRefineMaps maps a workgroup.
+constexpr int kRefineMaps = 12;
+
+__global__ void __launch_bounds__(64)
+    k_fringe_refine(const float2* __restrict__ F, const float2* __restrict__ tw,
+                    xc_fringe_peak* __restrict__ peaks, int n_maps, int n_sub, int R, int D,
+                    int n_chan, double dnu, double t_int) {
+  __shared__ float2 pts[5 * kRefineMaps];
+  const int m = threadIdx.x / 5, k = threadIdx.x - 5 * m;
+  const int map_id = blockIdx.x * kRefineMaps + m;
+  const bool live = m < kRefineMaps && map_id < n_maps;
+  int pr = 0, pd = 0;
+  if (live) {
+    const float2* Fm = F + (size_t)map_id * n_sub * D;
+    const unsigned long long key = *peak_key(peaks + map_id);
+    // (no candidate at all: bin 0, whose values the result then reports)
+    const unsigned pi = key ? 0xffffffffu - (unsigned)key : 0u;
+    pr = (int)(pi / (unsigned)D);
+    pd = (int)(pi - (unsigned)pr * D);
     const int rr = k == 3 ? (pr + R - 1) % R : k == 4 ? (pr + 1) % R : pr;
     const int dd = k == 1 ? (pd + D - 1) % D : k == 2 ? (pd + 1) % D : pd;
-    pts[k] = rate_point(Fm, tw, n_sub, R, D, rr, dd);
+    pts[threadIdx.x] = rate_point(Fm, tw, n_sub, R, D, rr, dd);
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
+  if (live && k == 0) {
+    const float2* z = pts + 5 * m;
     auto mag = [](float2 z) { return sqrtf(z.x * z.x + z.y * z.y); };
-    const float a0 = mag(pts[0]);
-    const float od = parabola_off(mag(pts[1]), a0, mag(pts[2]));
-    const float orr = parabola_off(mag(pts[3]), a0, mag(pts[4]));
+    const float a0 = mag(z[0]);
+    const float od = parabola_off(mag(z[1]), a0, mag(z[2]));
+    const float orr = parabola_off(mag(z[3]), a0, mag(z[4]));
     const int ds = signed_bin(pd, D), rs = signed_bin(pr, R);
     xc_fringe_peak p;
     p.delay_bin = ds;
     p.rate_bin = rs;
     p.amp = a0 / ((float)n_chan * (float)n_sub);
-    p.phase = atan2f(pts[0].y, pts[0].x);
+    p.phase = atan2f(z[0].y, z[0].x);
     p.delay_off = od;
     p.rate_off = orr;
     p.delay_s = ((double)ds + (double)od) / ((double)D * dnu);
@@ -268,42 +313,64 @@ static hipError_t allow_lds(K kernel, size_t bytes, std::atomic<bool> (&done)[64
   return e;
 }
 
-template <int D>
-static hipError_t launch_delay_d(const float2* vis, float2* F, const float2* tw, int n_sub,
-                                 int n_sb, int nbl, int n_chan, hipStream_t s) {
+template <int D, bool HALF>
+static hipError_t launch_delay_h(const xc_fringe_setup* fs, const float2* vis, float2* F,
+                                 const float2* tw, xc_fringe_peak* peaks, hipStream_t s) {
   using Gm = RowGeom<D>;
   static std::atomic<bool> done[64];
-  hipError_t e = allow_lds(k_fringe_delay<D>, Gm::lds_bytes, done);
+  hipError_t e = allow_lds(k_fringe_delay<D, HALF>, Gm::lds_bytes, done);
   if (e != hipSuccess) return e;
-  const long rows = (long)n_sub * n_sb * nbl;
+  const long n_maps = (long)fs->n_subbands * fs->n_baselines, rows = fs->n_subints * n_maps;
   const long per_wg = (long)Gm::G * kDelayIters;
-  hipLaunchKernelGGL(k_fringe_delay<D>, dim3((unsigned)((rows + per_wg - 1) / per_wg)),
-                     dim3(Gm::WG), Gm::lds_bytes, s, vis, F, tw, n_sub, n_sb, nbl, n_chan);
+  hipLaunchKernelGGL((k_fringe_delay<D, HALF>), dim3((unsigned)((rows + per_wg - 1) / per_wg)),
+                     dim3(Gm::WG), Gm::lds_bytes, s, vis, F, tw, peaks, fs->n_subints,
+                     (int)n_maps, fs->n_chan);
+  return hipGetLastError();
+}
+
+template <int D>
+static hipError_t launch_delay_d(const xc_fringe_setup* fs, const float2* vis, float2* F,
+                                 const float2* tw, xc_fringe_peak* peaks, hipStream_t s) {
+  return fs->n_chan <= D / 2 ? launch_delay_h<D, true>(fs, vis, F, tw, peaks, s)
+                             : launch_delay_h<D, false>(fs, vis, F, tw, peaks, s);
+}
+
+template <int R, bool HALF>
+static hipError_t launch_rate_h(const xc_fringe_setup* fs, const float2* F, const float2* tw,
+                                xc_fringe_peak* peaks, float2* map, hipStream_t s) {
+  static std::atomic<bool> done[64];
+  hipError_t e = allow_lds(k_fringe_rate<R, HALF>, RateGeom<R>::lds_bytes, done);
+  if (e != hipSuccess) return e;
+  // Chunks of columns (powers of two of rounds): down to two rounds a workgroup
+  // until the maps' workgroups fill the GPU some ten times
+  const long maps = (long)fs->n_subbands * fs->n_baselines;
+  int cols = fs->delay_len;
+  while (cols > 2 * RateGeom<R>::GC && maps * (fs->delay_len / cols) < 8192) cols /= 2;
+  hipLaunchKernelGGL((k_fringe_rate<R, HALF>), dim3((unsigned)maps, fs->delay_len / cols),
+                     dim3(kFringeThreads), RateGeom<R>::lds_bytes, s, F, tw, peaks, map,
+                     fs->n_subints, fs->delay_len, cols, fs->delay_win, fs->rate_win);
+  e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_fringe_refine, dim3((unsigned)((maps + kRefineMaps - 1) / kRefineMaps)),
+                     dim3(64), 0, s, F, tw, peaks, (int)maps, fs->n_subints, R, fs->delay_len,
+                     fs->n_chan, fs->chan_width_hz, fs->t_int_s);
   return hipGetLastError();
 }
 
 template <int R>
 static hipError_t launch_rate_r(const xc_fringe_setup* fs, const float2* F, const float2* tw,
                                 xc_fringe_peak* peaks, float2* map, hipStream_t s) {
-  static std::atomic<bool> done[64];
-  hipError_t e = allow_lds(k_fringe_rate<R>, RateGeom<R>::lds_bytes, done);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_fringe_rate<R>, dim3(fs->n_subbands * fs->n_baselines),
-                     dim3(kFringeThreads), RateGeom<R>::lds_bytes, s, F, tw, peaks, map,
-                     fs->n_subints, fs->delay_len, fs->n_chan, fs->delay_win, fs->rate_win,
-                     fs->chan_width_hz, fs->t_int_s);
-  return hipGetLastError();
+  if constexpr (R >= 2)
+    if (fs->n_subints <= R / 2) return launch_rate_h<R, true>(fs, F, tw, peaks, map, s);
+  return launch_rate_h<R, false>(fs, F, tw, peaks, map, s);
 }
 
 hipError_t launch_fringe(const xc_fringe_setup* fs, const float2* vis, float2* F,
                          const float2* tw, xc_fringe_peak* peaks, float2* map, hipStream_t s) {
   hipError_t e;
   switch (fs->delay_len) {
-#define XC_DCASE(DD)                                                                        \
-  case DD:                                                                                  \
-    e = launch_delay_d<DD>(vis, F, tw, fs->n_subints, fs->n_subbands, fs->n_baselines,      \
-                           fs->n_chan, s);                                                  \
-    break;
+#define XC_DCASE(DD) \
+  case DD: e = launch_delay_d<DD>(fs, vis, F, tw, peaks, s); break;
     XC_DCASE(256) XC_DCASE(512) XC_DCASE(1024) XC_DCASE(2048) XC_DCASE(4096) XC_DCASE(8192)
     XC_DCASE(16384)
 #undef XC_DCASE

@@ -212,10 +212,35 @@ constexpr int pad_off(int r) {
   return r * S + (r * S) / 32;
 }
 
+// Where entry i of a frame's exchange buffer sits.  PadIdx: one buffer per frame,
+// padded as above (pad_off).  ColIdx: the buffers of GC transforms interleaved,
+// entry i of all of them side by side, for lanes that hold neighbouring
+// transforms: a half-wave then reads and writes 32 neighbours, where separate
+// buffers (1056 bytes apart at 128 points) put 8 lanes on a bank.
+// (16 neighbours and two entries per half-wave: the entries of one run of 16
+// stay 16 places apart, and neighbouring runs 16 more, so that the two differ.)
+struct PadIdx {
+  __device__ static int at(int i) { return lds_pad(i); }
+  template <int S>
+  __device__ static constexpr int off(int r) {
+    return pad_off<S>(r);
+  }
+};
+template <int GC>
+struct ColIdx {
+  static_assert(GC >= 16, "at least 16 neighbouring transforms");
+  static constexpr int P = GC < 32 ? 16 : 0;
+  __device__ static int at(int i) { return i * GC + (i >> 4) * P; }
+  template <int S>
+  __device__ static constexpr int off(int r) {
+    return r * S * GC + ((r * S) >> 4) * P;
+  }
+};
+
 // One Stockham pass of radix R with sub-transform length Ns over a frame of N
 // points.  On entry v[b + r B] (B = E/R) is input r of butterfly j = t + b T;
 // the outputs are written to lds; the caller synchronises.
-template <int N, int T, int E, int R, int Ns, class TW>
+template <int N, int T, int E, int R, int Ns, class IX = PadIdx, class TW>
 __device__ inline void stockham_pass(float2 (&v)[E], float2* lds, const TW& tw, int t) {
   constexpr int B = E / R;
   static_assert(B * R == E, "radix must divide the per-thread count");
@@ -232,22 +257,22 @@ __device__ inline void stockham_pass(float2 (&v)[E], float2* lds, const TW& tw, 
     }
     Dft<R>::run(u);
     const int idx = (j / Ns) * Ns * R + (j % Ns);
-    float2* o = lds + lds_pad(idx);
+    float2* o = lds + IX::at(idx);
 #pragma unroll
-    for (int r = 0; r < R; ++r) o[pad_off<Ns>(r)] = u[r];
+    for (int r = 0; r < R; ++r) o[IX::template off<Ns>(r)] = u[r];
   }
 }
 
 // Gather the inputs of the next pass (radix R) from lds: v[b + r B] = x[j + r N / R].
-template <int N, int T, int E, int R>
+template <int N, int T, int E, int R, class IX = PadIdx>
 __device__ inline void stockham_gather(float2 (&v)[E], const float2* lds, int t) {
   constexpr int B = E / R;
 #pragma unroll
   for (int b = 0; b < B; ++b) {
     const int j = t + b * T;
-    const float2* x = lds + lds_pad(j);
+    const float2* x = lds + IX::at(j);
 #pragma unroll
-    for (int r = 0; r < R; ++r) v[b + r * B] = x[pad_off<N / R>(r)];
+    for (int r = 0; r < R; ++r) v[b + r * B] = x[IX::template off<N / R>(r)];
   }
 }
 
@@ -295,27 +320,27 @@ template <> struct FftPlan<16384> { static constexpr int T = 1024, E = 16; };
 // On entry v[e] = x[t + e T]; on exit v[b + r B_last] = X[t + b T + r N / 16].
 // `lds` holds lds_words<N>() float2; the group's threads synchronise with
 // __syncthreads (the whole workgroup runs the same pass sequence).
-template <int N, class TW>
+template <int N, class IX = PadIdx, class TW>
 __device__ inline void fft_forward(float2 (&v)[FftPlan<N>::E], float2* lds, const TW& tw, int t) {
   constexpr int T = FftPlan<N>::T, E = FftPlan<N>::E;
   constexpr int L2 = __builtin_ctz(N);
   // number of radix-16 passes after the first (mixed) pass
   constexpr int n16 = (L2 / 4) - ((L2 % 4) == 0 ? 1 : 0);
   constexpr int R0 = first_radix<N>();
-  stockham_pass<N, T, E, R0, 1>(v, lds, tw, t);
+  stockham_pass<N, T, E, R0, 1, IX>(v, lds, tw, t);
   __syncthreads();
-  stockham_gather<N, T, E, 16>(v, lds, t);
+  stockham_gather<N, T, E, 16, IX>(v, lds, t);
   if constexpr (n16 >= 2) {
     __syncthreads();
-    stockham_pass<N, T, E, 16, R0>(v, lds, tw, t);
+    stockham_pass<N, T, E, 16, R0, IX>(v, lds, tw, t);
     __syncthreads();
-    stockham_gather<N, T, E, 16>(v, lds, t);
+    stockham_gather<N, T, E, 16, IX>(v, lds, t);
   }
   if constexpr (n16 >= 3) {
     __syncthreads();
-    stockham_pass<N, T, E, 16, R0 * 16>(v, lds, tw, t);
+    stockham_pass<N, T, E, 16, R0 * 16, IX>(v, lds, tw, t);
     __syncthreads();
-    stockham_gather<N, T, E, 16>(v, lds, t);
+    stockham_gather<N, T, E, 16, IX>(v, lds, t);
   }
   static_assert(n16 <= 3, "plan supports up to 3 radix-16 passes after the first");
   stockham_last<N, T, E, 16>(v, tw, t);
