@@ -341,14 +341,13 @@ int plan_fused(xc_ctx* c, const xc_job* jobs, int n, int lanes, FPlan& F) {
         it.slot_stride = L.slot_stride;
         it.task0 = R.ntasks;
         if (g.W == kFstageMatrix) {
-          it.spt = fmat_subbands_per_task(g.N, s.n_stations, s.n_subbands, s.n_pols,
-                                          it.nf);
-          R.ntasks += fmat_tasks(g.N, s.n_stations, s.n_subbands, it.nf, it.spt);
+          it.ipt = fmat_inputs_per_task(g.N, s.n_stations, s.n_subbands, s.n_pols, it.nf);
+          R.ntasks += fmat_tasks(g.N, s.n_stations, s.n_subbands * s.n_pols, it.nf, it.ipt);
         } else {
           R.ntasks += fstage_fused_tasks(g.N, g.W, s.n_stations, s.n_subbands * s.n_pols, it.nf);
         }
         it.dblk0 = R.dblocks;
-        R.dblocks += delays_fused_blocks(it.nf, s.n_subbands);
+        R.dblocks += delays_fused_blocks(it.nf, s.n_stations, s.n_subbands);
         const int Mp = (M + 3) / 4 * 4;
         if (R.xc.empty() || R.xc.back().Mp != Mp)
           R.xc.push_back({Mp, (int)F.items.size() - R.first, 0, 0});

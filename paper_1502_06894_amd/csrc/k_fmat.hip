@@ -201,15 +201,15 @@ __device__ inline void dft32_half(float2 (&a)[16], float2 (&b)[16]) {
 
 constexpr int kMatInputs = 4;   // inputs of a task
 
-// One task: station s, frames fg .. fg + FPG - 1 (this wave: f0 ..), subbands
-// sb_lo .. sb_hi - 1 with all their pols (at most kMatInputs inputs).  wave:
-// its number in the workgroup, w: its place in its frame (0 for N <= 2048).
+// One task: station s, frames fg .. fg + FPG - 1 (this wave: f0 ..), inputs
+// in_lo .. in_hi - 1 (at most kMatInputs; input = subband, pol).  wave: its
+// number in the workgroup, w: its place in its frame (0 for N <= 2048).
 template <int N, int OUT>
 __device__ __forceinline__ void fmat_task(const DevJob& Jb, const DelayRec* __restrict__ drec,
                                           const PhaseRec* __restrict__ prec,
                                           void* __restrict__ spec,
                                           const int8_t* __restrict__ scale_exp, int nf, int s,
-                                          int fg, int f0, int sb_lo, int sb_hi, int wave, int w,
+                                          int fg, int f0, int in_lo, int in_hi, int wave, int w,
                                           unsigned char* lds, float* rows, float2* fdt,
                                           const float2* __restrict__ tw) {
   using G = MGeom<N>;
@@ -260,7 +260,7 @@ __device__ __forceinline__ void fmat_task(const DevJob& Jb, const DelayRec* __re
     pb[i] = ((uint32_t)ip >> spw) * 4;
     sh0[i] = 2 * (ip & ((1 << spw) - 1)) * Jb.C;
   }
-  const int n_in = (sb_hi - sb_lo) * P;
+  const int n_in = in_hi - in_lo;
 #pragma unroll
   for (int eb = 0; eb < RAD / 16; ++eb) {
     uint32_t wv[4][8];
@@ -286,7 +286,7 @@ __device__ __forceinline__ void fmat_task(const DevJob& Jb, const DelayRec* __re
 #pragma unroll
     for (int k = 0; k < kMatInputs; ++k)
       if (k < n_in) {
-        const int map2 = 2 * Jb.stream_map[sb_lo * P + k];
+        const int map2 = 2 * Jb.stream_map[in_lo + k];
 #pragma unroll
         for (int m = 0; m < 32; ++m) {
           // two bits in at the top: 16 times, so the first ends at the bottom
@@ -312,7 +312,8 @@ __device__ __forceinline__ void fmat_task(const DevJob& Jb, const DelayRec* __re
   }
 
 #pragma unroll 1
-  for (int sb = sb_lo; sb < sb_hi; ++sb) {
+  for (int sb = in_lo / P; sb * P < in_hi; ++sb) {
+    const int p_lo = max(in_lo - sb * P, 0), p_hi = min(in_hi - sb * P, P);
     const PhaseRec* ph = prec + ((size_t)s * n_sb + sb) * nf;
 #pragma unroll 1
     for (int hh = 0; hh < G::HH; ++hh) {
@@ -362,8 +363,8 @@ __device__ __forceinline__ void fmat_task(const DevJob& Jb, const DelayRec* __re
       }
       __syncthreads();
 #pragma unroll 1
-      for (int p = 0; p < P; ++p) {
-        const int k_in = (sb - sb_lo) * P + p;
+      for (int p = p_lo; p < p_hi; ++p) {
+        const int k_in = sb * P + p - in_lo;
         uint32_t cd[KG];
 #pragma unroll
         for (int i = 0; i < KG; ++i) {
@@ -621,7 +622,7 @@ __device__ __forceinline__ void fmat_tab(unsigned char* lds, const float2* __res
   }
 }
 
-// Tasks (station, group of FPG frames, group of spt subbands), the last
+// Tasks (station, group of FPG frames, group of ipt inputs), the last
 // fastest; a workgroup takes every n-th.  Tasks cost the same, so they are not
 // fetched from a counter.
 template <int N, int OUT>
@@ -629,7 +630,7 @@ __global__ void __attribute__((amdgpu_flat_work_group_size(1, MGeom<N>::WG),
                                amdgpu_waves_per_eu(MGeom<N>::EU)))
     k_fmat(const DevJob* __restrict__ job, const DelayRec* __restrict__ drec,
            const PhaseRec* __restrict__ prec, const float2* __restrict__ tw,
-           void* __restrict__ spec, const int8_t* __restrict__ scale_exp, int nf, int spt) {
+           void* __restrict__ spec, const int8_t* __restrict__ scale_exp, int nf, int ipt) {
   using G = MGeom<N>;
   extern __shared__ __attribute__((aligned(16))) unsigned char fmat_lds[];
   const DevJob& J = *job;
@@ -638,15 +639,15 @@ __global__ void __attribute__((amdgpu_flat_work_group_size(1, MGeom<N>::WG),
   float* rows = reinterpret_cast<float*>(fmat_lds + G::rows_off) + unit * G::unit_f;
   float2* fdt = reinterpret_cast<float2*>(fmat_lds + G::fd_off) + wave * G::fd_n;
   fmat_tab<N>(fmat_lds, tw);
-  const int n_sb = J.n_subbands;
-  const int n_ig = (n_sb + spt - 1) / spt, per_station = (nf + G::FPG - 1) / G::FPG * n_ig;
+  const int n_in = J.n_inputs;
+  const int n_ig = (n_in + ipt - 1) / ipt, per_station = (nf + G::FPG - 1) / G::FPG * n_ig;
   const int n_tasks = per_station * J.n_stations;
 #pragma unroll 1
   for (int task = blockIdx.x; task < n_tasks; task += gridDim.x) {
     const int s = task / per_station, rem = task - s * per_station;
-    const int grp = rem / n_ig, sb = (rem - grp * n_ig) * spt;
+    const int grp = rem / n_ig, in = (rem - grp * n_ig) * ipt;
     fmat_task<N, OUT>(J, drec, prec, spec, scale_exp, nf, s, grp * G::FPG,
-                      grp * G::FPG + unit * G::FPW, sb, min(sb + spt, n_sb), wave, wave % G::WPF,
+                      grp * G::FPG + unit * G::FPW, in, min(in + ipt, n_in), wave, wave % G::WPF,
                       fmat_lds, rows, fdt, tw);
   }
 }
@@ -676,13 +677,13 @@ __global__ void __attribute__((amdgpu_flat_work_group_size(1, MGeom<N>::WG),
         hi = mid - 1;
     }
     const DevJob& J = *(const DevJob*)&items[lo].jd;
-    const int nf = items[lo].nf, n_sb = J.n_subbands, spt = items[lo].spt;
-    const int n_ig = (n_sb + spt - 1) / spt, per_station = (nf + G::FPG - 1) / G::FPG * n_ig;
+    const int nf = items[lo].nf, n_in = J.n_inputs, ipt = items[lo].ipt;
+    const int n_ig = (n_in + ipt - 1) / ipt, per_station = (nf + G::FPG - 1) / G::FPG * n_ig;
     const int local = task - items[lo].task0;
     const int s = local / per_station, rem = local - s * per_station;
-    const int grp = rem / n_ig, sb = (rem - grp * n_ig) * spt;
+    const int grp = rem / n_ig, in = (rem - grp * n_ig) * ipt;
     fmat_task<N, kOutF32>(J, items[lo].drec, items[lo].prec, items[lo].spec, nullptr, nf, s,
-                          grp * G::FPG, grp * G::FPG + unit * G::FPW, sb, min(sb + spt, n_sb),
+                          grp * G::FPG, grp * G::FPG + unit * G::FPW, in, min(in + ipt, n_in),
                           wave, wave % G::WPF, fmat_lds, rows, fdt, tw);
   }
 }
@@ -716,11 +717,11 @@ hipError_t launch_fmat_no(const DevJob* job, int n_stations, int n_subbands, int
   int res = 0;
   hipError_t e = resident_groups(k_fmat<N, OUT>, G::WG, G::lds_bytes, cache, res);
   if (e != hipSuccess) return e;
-  const int spt = fmat_subbands_per_task(N, n_stations, n_subbands, n_pols, nf);
-  const int tasks = fmat_tasks(N, n_stations, n_subbands, nf, spt);
+  const int ipt = fmat_inputs_per_task(N, n_stations, n_subbands, n_pols, nf);
+  const int tasks = fmat_tasks(N, n_stations, n_subbands * n_pols, nf, ipt);
   if (tasks <= 0) return hipSuccess;
   hipLaunchKernelGGL((k_fmat<N, OUT>), dim3(tasks < res ? tasks : res), dim3(G::WG), G::lds_bytes,
-                     s, job, drec, prec, tw, spec, scale_exp, nf, spt);
+                     s, job, drec, prec, tw, spec, scale_exp, nf, ipt);
   return hipGetLastError();
 }
 
@@ -759,11 +760,12 @@ static_assert(MGeom<256>::FPG == 32 && MGeom<2048>::FPG == 4 && MGeom<4096>::FPG
                   MGeom<8192>::FPG == 1 && MGeom<16384>::FPG == 1,
               "fmat_frames_per_task mirrors MGeom");
 
-int fmat_subbands_per_task(int N, int n_stations, int n_subbands, int n_pols, int nf) {
+int fmat_inputs_per_task(int N, int n_stations, int n_subbands, int n_pols, int nf) {
   // A task's words and phasors are set up once for its inputs, at about 0.3 of an
-  // input's time (array_fp16-like jobs: 7.0 ms at four inputs a task, 8.5 at one);
-  // few tasks leave the last round of the 1024 resident workgroups half empty.  The
-  // split of the subbands that takes the least time, the fewest tasks on a tie.
+  // input's time (32 stations x 4 inputs of 8192 points: 7.0 ms at four inputs a
+  // task, 8.5 at one); few tasks leave the last round of the 1024 resident
+  // workgroups half empty.  The split of the subbands (down to single pols where
+  // all tasks fit one round) that takes the least time, the fewest tasks on a tie.
   const int F = fmat_frames_per_task(N);
   const long base = (long)n_stations * ((nf + F - 1) / F);
   int best = 1;
@@ -775,15 +777,15 @@ int fmat_subbands_per_task(int N, int n_stations, int n_subbands, int n_pols, in
     const double t = (double)rounds * ((double)n_subbands * n_pols / n + 0.3);
     if (best_t == 0.0 || t < 0.97 * best_t) {
       best_t = t;
-      best = spt;
+      best = spt * n_pols;
     }
   }
-  return best;
+  return base * n_subbands * n_pols <= 1024 ? 1 : best;
 }
 
-int fmat_tasks(int N, int n_stations, int n_subbands, int nf, int spt) {
+int fmat_tasks(int N, int n_stations, int n_inputs, int nf, int ipt) {
   const int F = fmat_frames_per_task(N);
-  return n_stations * ((nf + F - 1) / F) * ((n_subbands + spt - 1) / spt);
+  return n_stations * ((nf + F - 1) / F) * ((n_inputs + ipt - 1) / ipt);
 }
 
 hipError_t launch_fmat(int N, const DevJob* job, int n_stations, int n_subbands, int n_pols,

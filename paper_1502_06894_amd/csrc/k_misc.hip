@@ -33,6 +33,26 @@ hipError_t launch_zero(unsigned long long* p, size_t n, hipStream_t s) {
   return hipGetLastError();
 }
 
+// Copy n 16-byte words from pinned host memory (a descriptor: a few KB) to the
+// device, then tell the host by writing seq to *done, also pinned.  One
+// workgroup, and no event: a copy command, or an event behind the kernel, keeps
+// the stream's next kernel waiting some 5 us, a sixth of a short call.
+__global__ void __launch_bounds__(1024)
+    k_upload(const uint4* src, uint4* __restrict__ dst, int n, unsigned long long* done,
+             unsigned long long seq) {
+  for (int i = threadIdx.x; i < n; i += 1024) dst[i] = src[i];
+  __syncthreads();
+  if (threadIdx.x == 0)
+    __hip_atomic_store(done, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+hipError_t launch_upload(const void* host, void* dst, size_t bytes, unsigned long long* done,
+                         unsigned long long seq, hipStream_t s) {
+  hipLaunchKernelGGL(k_upload, dim3(1), dim3(1024), 0, s, static_cast<const uint4*>(host),
+                     static_cast<uint4*>(dst), (int)(bytes / 16), done, seq);
+  return hipGetLastError();
+}
+
 // Delay record (subband 0 only) and phase record of frame fl of a block
 // starting at frame f0, station s, subband sb; the frame's validity for
 // subband 0.
@@ -78,33 +98,38 @@ __device__ inline bool delay_phase_records(const DevJob& J, int s, int sb, int64
   return ok;
 }
 
-// One workgroup: the frames of a 64-frame chunk (one a lane) of every station
-// (a wave each) for one subband.  For subband 0 the stations' validity masks
-// then meet in LDS and each station pair's count of common valid frames is
-// added to its total (wst, integers: exact in any order), so that no second
-// launch reads the records back.
+// One workgroup: 64-frame chunks (a frame a lane) of every station (a wave each)
+// for one subband, as many chunks as its 16 waves have room for.  For subband 0
+// the stations' validity masks then meet in LDS and each station pair's count of
+// common valid frames is added to its total (wst, integers: exact in any order),
+// so that no second launch reads the records back; the chunks of a workgroup
+// add once (31250 frames of two stations: one add a chunk made 11.9 us of it).
 constexpr int kDelayFrames = 64;
-constexpr int kDelayWaves = 16;         // at most, in one workgroup
+constexpr int kDelayWaves = 16;
+__host__ __device__ inline int delay_chunks(int n_stations) {   // of a workgroup
+  return n_stations < kDelayWaves ? kDelayWaves / n_stations : 1;
+}
 
-__device__ __forceinline__ void delays_chunk(const DevJob& J, int64_t f0, int chunk, int sb, int nf,
+__device__ __forceinline__ void delays_chunk(const DevJob& J, int64_t f0, int block, int sb, int nf,
                                              DelayRec* __restrict__ drec,
                                              PhaseRec* __restrict__ prec,
                                              unsigned long long* __restrict__ wst) {
-  __shared__ unsigned long long mask[kMaxStations];
-  const int S = J.n_stations;
+  __shared__ unsigned long long mask[kMaxStations];   // [chunk][station]
+  const int S = J.n_stations, chunks = delay_chunks(S);
   const int lane = threadIdx.x & 63, waves = blockDim.x >> 6;
-  const int fl = chunk * kDelayFrames + lane;
-  for (int s = threadIdx.x >> 6; s < S; s += waves) {
-    const bool ok = fl < nf && delay_phase_records(J, s, sb, f0, fl, nf, drec, prec);
+  for (int w = threadIdx.x >> 6; w < S * chunks; w += waves) {
+    const int c = w / S, fl = (block * chunks + c) * kDelayFrames + lane;
+    const bool ok = fl < nf && delay_phase_records(J, w - c * S, sb, f0, fl, nf, drec, prec);
     const unsigned long long m = __ballot(ok);
-    if (lane == 0) mask[s] = m;
+    if (lane == 0) mask[w] = m;
   }
   if (sb != 0 || !wst) return;
   __syncthreads();
   for (int p = threadIdx.x; p < S * S; p += blockDim.x) {
     const int i = p / S, j = p - i * S;
     if (j < i) continue;
-    const int n = __popcll(mask[i] & mask[j]);
+    int n = 0;
+    for (int c = 0; c < chunks; ++c) n += __popcll(mask[c * S + i] & mask[c * S + j]);
     if (n) atomicAdd(&wst[p], (unsigned long long)n);
   }
 }
@@ -123,21 +148,21 @@ __global__ void __launch_bounds__(64 * kDelayWaves)
 hipError_t launch_delays(const DevJob* job, int n_stations, int n_subbands, int64_t f0, int nf,
                          DelayRec* drec, PhaseRec* prec, unsigned* ctr, unsigned long long* wst,
                          hipStream_t s) {
-  const dim3 grid((nf + kDelayFrames - 1) / kDelayFrames, n_subbands);
-  const int waves = n_stations < kDelayWaves ? n_stations : kDelayWaves;
+  const int chunks = delay_chunks(n_stations), frames = chunks * kDelayFrames;
+  const dim3 grid((nf + frames - 1) / frames, n_subbands);
+  const int waves = n_stations < kDelayWaves ? n_stations * chunks : kDelayWaves;
   hipLaunchKernelGGL(k_delays, grid, dim3(64 * waves), 0, s, job, f0, nf, drec, prec, ctr, wst);
   return hipGetLastError();
 }
 
-constexpr int kDelayFusedThreads = 256;
-
-int delays_fused_blocks(int nf, int n_subbands) {
-  return (nf + kDelayFrames - 1) / kDelayFrames * n_subbands;
+int delays_fused_blocks(int nf, int n_stations, int n_subbands) {
+  const int frames = delay_chunks(n_stations) * kDelayFrames;
+  return (nf + frames - 1) / frames * n_subbands;
 }
 
 // k_delays over the blocks of a fused round: workgroup -> (item, frame chunk,
 // subband).
-__global__ void __launch_bounds__(kDelayFusedThreads)
+__global__ void __launch_bounds__(64 * kDelayWaves)
     k_delays_fused(const FusedItem* __restrict__ items, int n_items, unsigned* __restrict__ ctr) {
   const int it = fused_find(items, n_items, (int)blockIdx.x,
                             [](const FusedItem& I) { return I.dblk0; });
@@ -146,7 +171,8 @@ __global__ void __launch_bounds__(kDelayFusedThreads)
     ctr[0] = 0u;
     ctr[1] = 0u;
   }
-  const int nfb = (I.nf + kDelayFrames - 1) / kDelayFrames;
+  const int frames = delay_chunks(I.jd.n_stations) * kDelayFrames;
+  const int nfb = (I.nf + frames - 1) / frames;
   const int local = (int)blockIdx.x - I.dblk0;
   delays_chunk(I.jd, I.f0, local % nfb, local / nfb, I.nf, I.drec, I.prec, I.wst);
 }
@@ -154,7 +180,7 @@ __global__ void __launch_bounds__(kDelayFusedThreads)
 hipError_t launch_delays_fused(const FusedItem* items, int n_items, int n_blocks, unsigned* ctr,
                                hipStream_t s) {
   if (n_blocks <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_delays_fused, dim3(n_blocks), dim3(kDelayFusedThreads), 0, s, items,
+  hipLaunchKernelGGL(k_delays_fused, dim3(n_blocks), dim3(64 * kDelayWaves), 0, s, items,
                      n_items, ctr);
   return hipGetLastError();
 }
@@ -176,9 +202,19 @@ __device__ inline void finalise_elem(const double2* __restrict__ vacc, int n_slo
   const int j = i + rem;
   const double w = (double)wst[(i / P) * S + (j / P)];
   double2 a = vacc[e];
-  // fixed slot order; the loads of eight slots are issued together (a job of
-  // few channels and baselines can have over a hundred slots)
+  // fixed slot order; the loads of eight slots are issued together, of 32 while
+  // there are that many (a job of few channels and baselines can have over a hundred)
   int q = 1;
+  for (; q + 32 <= n_slots; q += 32) {
+    double2 b[32];
+#pragma unroll
+    for (int u = 0; u < 32; ++u) b[u] = vacc[e + (size_t)(q + u) * slot_stride];
+#pragma unroll
+    for (int u = 0; u < 32; ++u) {
+      a.x += b[u].x;
+      a.y += b[u].y;
+    }
+  }
   for (; q + 8 <= n_slots; q += 8) {
     double2 b[8];
 #pragma unroll

@@ -28,7 +28,7 @@ struct FusedItem {
   int64_t f0;              // first frame of the block
   int32_t nf;              // frames in the block
   int32_t fps;             // X stage: frames per FP32 slice
-  int32_t spt;             // matrix-core F stage: subbands per task
+  int32_t ipt;             // matrix-core F stage: inputs per task
   int32_t n_init;          // X stage: accumulator slots already written
   int32_t task0;           // F stage: tasks before this item
   int32_t dblk0;           // delay kernel: workgroups before this item
@@ -60,6 +60,10 @@ __device__ inline FusedItemsK fused_const(const FusedItem* items) { return (Fuse
 // A0: frame_ok[f] = sync word of recording frame f is good.
 hipError_t launch_ingest(const uint32_t* words, int64_t n_frames, uint8_t* frame_ok,
                          hipStream_t s);
+// Copy `bytes` (a multiple of 16) of pinned host memory to 16-byte aligned
+// device memory, then set the pinned word *done to seq.
+hipError_t launch_upload(const void* host, void* dst, size_t bytes, unsigned long long* done,
+                         unsigned long long seq, hipStream_t s);
 // Zero n 64-bit words.
 hipError_t launch_zero(unsigned long long* p, size_t n, hipStream_t s);
 // A1: delay and phase records for frames f0 .. f0+nf-1 of every station; also
@@ -154,15 +158,15 @@ hipError_t launch_fstage(int N, const DevJob* job, int n_stations, int n_subband
                          void* spec, const int8_t* scale_exp, int nf, int waves, int out,
                          unsigned* ctr, float2* scratch, hipStream_t s);
 // The F stage on the matrix cores (32768 points: FP32 spectra; the job must pass
-// fstage_matrix_ok): its tasks, each of spt subbands of a station and frame group.
+// fstage_matrix_ok): its tasks, each of ipt inputs of a station and frame group.
 hipError_t launch_fmat(int N, const DevJob* job, int n_stations, int n_subbands, int n_pols,
                        const DelayRec* drec, const PhaseRec* prec, const float2* tw, void* spec,
                        const int8_t* scale_exp, int nf, int out, hipStream_t s);
 hipError_t launch_fmat_fused(int N, const FusedItem* items, int n_items, int n_tasks,
                              const float2* tw, hipStream_t s);
-int fmat_subbands_per_task(int N, int n_stations, int n_subbands, int n_pols, int nf);
+int fmat_inputs_per_task(int N, int n_stations, int n_subbands, int n_pols, int nf);
 int fmat_frames_per_task(int N);
-int fmat_tasks(int N, int n_stations, int n_subbands, int nf, int spt);
+int fmat_tasks(int N, int n_stations, int n_inputs, int nf, int ipt);
 // Scratch the F stage needs for nf frames (nonzero for N = 32768: its four-step
 // FFT goes through memory).
 size_t fstage_scratch_bytes(int N, int n_stations, int n_inputs, int nf, int out);
@@ -211,8 +215,8 @@ hipError_t launch_finalise(const double2* vacc, int n_slots, size_t slot_stride,
 // ctr[0], ctr[1]).
 hipError_t launch_delays_fused(const FusedItem* items, int n_items, int n_blocks, unsigned* ctr,
                                hipStream_t s);
-// Workgroups launch_delays_fused needs for an item of nf frames and n_sb subbands.
-int delays_fused_blocks(int nf, int n_subbands);
+// Workgroups launch_delays_fused needs for an item of nf frames, S stations, n_sb subbands.
+int delays_fused_blocks(int nf, int n_stations, int n_subbands);
 // F stage over every item's block (all items of FFT length N, variant `waves`).
 hipError_t launch_fstage_fused(int N, int waves, const FusedItem* items, int n_items,
                                int n_tasks, const float2* tw, unsigned* ctr, hipStream_t s);

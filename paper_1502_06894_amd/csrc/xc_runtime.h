@@ -57,8 +57,9 @@ struct xc_ctx {
   size_t prof_used = 0;
   float2* d_tw = nullptr;                    // FFT twiddles, kTwiddleN entries
   int scratch_rc = 0;                        // lookup of the allocation-free scratch (hipError_t)
-  unsigned char* h_stage = nullptr;          // kSlots x kSlotBytes pinned
-  hipEvent_t ev[xc::kSlots] = {};
+  unsigned char* h_stage = nullptr;          // kSlots x kSlotBytes pinned, then one word per slot:
+  unsigned long long slot_seq[xc::kSlots] = {};   // the upload that last used the slot is done
+                                             // when the slot's word says slot_seq
   int next_slot = 0;
   std::vector<hipStream_t> lanes;            // batch lanes (default priority)
   std::vector<hipEvent_t> lane_ev;           // join events, one per lane

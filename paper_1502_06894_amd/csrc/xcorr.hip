@@ -4,7 +4,9 @@
 
 #include <algorithm>
 #include <atomic>
+#include <chrono>
 #include <mutex>
+#include <thread>
 
 #include "xc_runtime.h"
 
@@ -299,21 +301,48 @@ void build_desc(const xc_setup* s, const xc_station* st, const Layout& L,
   }
 }
 
+static unsigned long long* slot_words(xc_ctx* c) {
+  return reinterpret_cast<unsigned long long*>(c->h_stage + (size_t)kSlots * kSlotBytes);
+}
+
+// Wait until the slot's last upload has read it (seldom: kSlots calls ahead of
+// the device): look a few thousand times, then every 20 us.  After 10 s without
+// it the device is asked for everything it still has, which reports an error
+// that would keep the word from changing.
+static hipError_t wait_slot(xc_ctx* c, int k) {
+  const unsigned long long* w = slot_words(c) + k;
+  auto done = [&] { return __atomic_load_n(w, __ATOMIC_ACQUIRE) == c->slot_seq[k]; };
+  for (int i = 0; i < 4096; ++i)
+    if (done()) return hipSuccess;
+  for (int i = 0; i < 500000; ++i) {
+    if (done()) return hipSuccess;
+    std::this_thread::sleep_for(std::chrono::microseconds(20));
+  }
+  const hipError_t e = hipDeviceSynchronize();
+  return e != hipSuccess ? e : done() ? hipSuccess : hipErrorUnknown;
+}
+
 int upload_desc(xc_ctx* c, const xc_setup* s, const xc_station* st, const Layout& L,
                 unsigned char* dev_desc, hipStream_t stream) {
   const size_t arena_off = align_up(L.desc_bytes), bytes = arena_off + L.wst_bytes;
   if (bytes > kSlotBytes) return fail(c, XC_E_INVAL, "descriptor too large");
   const int k = c->next_slot;
   c->next_slot = (k + 1) % kSlots;
-  hipError_t e = hipEventSynchronize(c->ev[k]);
-  if (e != hipSuccess) return hip_fail(c, e, "hipEventSynchronize");
+  hipError_t e = wait_slot(c, k);
+  if (e != hipSuccess) return hip_fail(c, e, "descriptor slot");
   unsigned char* h = c->h_stage + (size_t)k * kSlotBytes;
   build_desc(s, st, L, dev_desc, h);
   memset(h + arena_off, 0, L.wst_bytes);
-  e = hipMemcpyAsync(dev_desc, h, bytes, hipMemcpyHostToDevice, stream);
+  const unsigned long long seq = c->slot_seq[k] + 1;
+  if (reinterpret_cast<uintptr_t>(dev_desc) % 16 == 0) {
+    e = launch_upload(h, dev_desc, bytes, slot_words(c) + k, seq, stream);
+  } else {   // (a workspace that starts on an odd address)
+    e = hipMemcpyAsync(dev_desc, h, bytes, hipMemcpyHostToDevice, stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(stream);
+    slot_words(c)[k] = seq;
+  }
   if (e != hipSuccess) return hip_fail(c, e, "descriptor upload");
-  e = hipEventRecord(c->ev[k], stream);
-  if (e != hipSuccess) return hip_fail(c, e, "hipEventRecord");
+  c->slot_seq[k] = seq;
   return XC_OK;
 }
 
@@ -525,10 +554,11 @@ int xc_create(xc_ctx** out, int hip_device) {
   if (e == hipSuccess)
     e = hipMemcpy(c->d_tw, tw.data(), sizeof(float2) * kTwiddleN, hipMemcpyHostToDevice);
   if (e == hipSuccess)
-    e = hipHostMalloc((void**)&c->h_stage, (size_t)kSlots * kSlotBytes, hipHostMallocDefault);
+    e = hipHostMalloc((void**)&c->h_stage,
+                      (size_t)kSlots * (kSlotBytes + sizeof(unsigned long long)),
+                      hipHostMallocDefault);
+  if (e == hipSuccess) memset(slot_words(c), 0, kSlots * sizeof(unsigned long long));
   if (e == hipSuccess) c->scratch_rc = (int)scratch_lookup(hip_device);
-  for (int k = 0; k < kSlots && e == hipSuccess; ++k)
-    e = hipEventCreateWithFlags(&c->ev[k], hipEventDisableTiming);
   if (e != hipSuccess) {
     xc_destroy(c);
     return XC_E_HIP;
@@ -545,11 +575,8 @@ void xc_destroy(xc_ctx* c) {
     (void)hipEventDestroy(t.a);
     (void)hipEventDestroy(t.b);
   }
-  for (int k = 0; k < kSlots; ++k)
-    if (c->ev[k]) {
-      (void)hipEventSynchronize(c->ev[k]);
-      (void)hipEventDestroy(c->ev[k]);
-    }
+  if (c->h_stage)
+    for (int k = 0; k < kSlots; ++k) (void)wait_slot(c, k);
   for (auto& g : c->graphs) hipGraphExecDestroy(g.exec);
   for (size_t i = 0; i < c->lanes.size(); ++i) {
     (void)hipStreamSynchronize(c->lanes[i]);
