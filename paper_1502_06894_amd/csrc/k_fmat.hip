@@ -62,8 +62,8 @@ namespace {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-// Shape of an N-point frame's transform.
-template <int N>
+// Shape of an N-point frame's transform; MATS matrices (the drift pass: two).
+template <int N, int MATS = 1>
 struct MGeom {
   // first radix: 16, or 32 at N = 32768, half of whose outputs k1 a pass (two
   // passes over the same codes; a pass's 16-channel runs are whole lines)
@@ -92,7 +92,7 @@ struct MGeom {
   static constexpr int fd_n = WPF > 1 ? 16 : FPW * (ROWS > 64 ? 8 : 16);   // a wave's bin phasors
   // LDS: the matrix (4 KB; 8 for radix 32), the units' rows, the waves' phasors
   static constexpr size_t lo_off = (size_t)KG * 1024;       // its lower terms
-  static constexpr size_t rows_off = 2 * lo_off;
+  static constexpr size_t rows_off = 2 * lo_off * MATS;
   static_assert(WAVES >= RAD / 4, "a wave forms four columns of the matrix");
   static constexpr size_t fd_off = rows_off + (size_t)UNITS * unit_f * sizeof(float);
   // WPF > 1: pass-2 twiddles exp(-2 pi i ta kb / L), [ta][kb] (LDS broadcasts: as scalar
@@ -102,7 +102,9 @@ struct MGeom {
   // waves per SIMD asked of the compiler: four (128 registers) leave the short transforms,
   // with several frames a lane, spilling: F stage of 256-point jobs 0.86 of the vector
   // kernel's time at two, 1.0 at four; 2048 and 16384 points 0.95 and 0.91 at two, 0.94 and 0.77 at four
-  static constexpr int EU = N <= 1024 ? 2 : 4;
+  // (the drift pass, with twice the accumulators: two at every length; asked for three
+  // it spills, 256- and 512-point drift jobs 1.07 and 1.12 of their time, 16384 1.10)
+  static constexpr int EU = N <= 1024 || MATS > 1 ? 2 : 4;
 };
 
 // x - round(x) as float: |result| <= 1/2 (half the rounding error of [0, 1))
@@ -201,6 +203,23 @@ __device__ inline void dft32_half(float2 (&a)[16], float2 (&b)[16]) {
 
 constexpr int kMatInputs = 4;   // inputs of a task
 
+// What the kernel writes besides the spectrum types: the delay-drift correction,
+// run after the regular pass on the stations that ask for it.  The window is
+// weighted by the ramp n - N / 2 = t + T (e - RAD / 2), so the first pass is t times
+// the regular product plus T times one with the matrix weighted by e - RAD / 2,
+// and the stored spectrum Y becomes (1 - rho) Y + (2 pi i rho k / N) Yr.
+// The vector kernel's drift pass likewise transforms twice, from single phasors.
+// Jobs of 5 stations (one corrected), 2 subbands, 2 polarisations and 2^23 samples
+// an input, whole, with the vector kernel's drift pass and with this one: 256 points 476 -> 445 us, 512 453 -> 419, 1024 443 -> 405, 2048 443 -> 408,
+// 8192 521 -> 508, 16384 605 -> 520 (4096: matrix_rate_ok).
+constexpr int kOutRate = 3;
+
+__device__ __forceinline__ void add_drift(float2* p, float2 yr, float rho, float k_over_n) {
+  const float2 old = *p;
+  const float a = 6.28318530717958648f * rho * k_over_n;
+  *p = make_float2((1.0f - rho) * old.x - a * yr.y, (1.0f - rho) * old.y + a * yr.x);
+}
+
 // One task: station s, frames fg .. fg + FPG - 1 (this wave: f0 ..), inputs
 // in_lo .. in_hi - 1 (at most kMatInputs; input = subband, pol).  wave: its
 // number in the workgroup, w: its place in its frame (0 for N <= 2048).
@@ -212,7 +231,8 @@ __device__ __forceinline__ void fmat_task(const DevJob& Jb, const DelayRec* __re
                                           int fg, int f0, int in_lo, int in_hi, int wave, int w,
                                           unsigned char* lds, float* rows, float2* fdt,
                                           const float2* __restrict__ tw) {
-  using G = MGeom<N>;
+  constexpr bool RATE = OUT == kOutRate, F32 = RATE || OUT == kOutF32;
+  using G = MGeom<N, RATE ? 2 : 1>;
   constexpr int RAD = G::RAD, KG = G::KG;
   constexpr int T = G::T, J = G::J, NF = G::NF, L = G::L, RS = G::RS, R = G::R, WPF = G::WPF;
   constexpr int RPL = WPF > 1 ? 1 : G::ROWS / 64;   // rows per lane after the exchange
@@ -330,22 +350,32 @@ __device__ __forceinline__ void fmat_task(const DevJob& Jb, const DelayRec* __re
         // 4 h + i % 4, which are given k1 = 8 h + i / 2 and re / im = i % 2
         const int row_k1 = 16 * hh + 8 * ((c >> 2) & 1) + 2 * (c >> 3) + ((c >> 1) & 1);
         const double row_im = (c & 1) ? 0.25 : 0.0;    // sin x = cos(x - 1/4 turn)
-        half4 hi, lo;                                  // upper code bit of both, lower of both
+        unsigned char* o = lds + (wave >> 1) * 1024 + lane * 16 + (wave & 1) * 8;
+        float a[2];
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
           const int e = 2 * (2 * wave + i) + h;
           const double ee = (double)(e - RAD / 2);
           const double off = (double)((e * row_k1) & (RAD - 1)) * (1.0 / RAD) + row_im;
-          const float a = __builtin_amdgcn_cosf(frac_c(fma(ee, fma(ee, a2, a1), -off)));
-          const half2 x = split_f16(a * kScaleX), y = split_f16(a * kScaleY);
-          hi[i] = x[0];
-          hi[i + 2] = y[0];
-          lo[i] = x[1];
-          lo[i + 2] = y[1];
+          a[i] = __builtin_amdgcn_cosf(frac_c(fma(ee, fma(ee, a2, a1), -off)));
         }
-        unsigned char* o = lds + (wave >> 1) * 1024 + lane * 16 + (wave & 1) * 8;
-        *reinterpret_cast<half4*>(o) = hi;
-        *reinterpret_cast<half4*>(o + G::lo_off) = lo;
+#pragma unroll
+        for (int m = 0; m < (RATE ? 2 : 1); ++m) {
+          half4 hi, lo;                                // upper code bit of both, lower of both
+#pragma unroll
+          for (int i = 0; i < 2; ++i) {
+            // (the drift pass's second matrix: the samples' ramp e - RAD / 2, over RAD / 2)
+            const float b =
+                m == 0 ? a[i] : a[i] * ((float)(2 * (2 * wave + i) + h - RAD / 2) * (2.f / RAD));
+            const half2 x = split_f16(b * kScaleX), y = split_f16(b * kScaleY);
+            hi[i] = x[0];
+            hi[i + 2] = y[0];
+            lo[i] = x[1];
+            lo[i + 2] = y[1];
+          }
+          *reinterpret_cast<half4*>(o + 2 * m * G::lo_off) = hi;
+          *reinterpret_cast<half4*>(o + (2 * m + 1) * G::lo_off) = lo;
+        }
       }
       float2 z[NF], S[NF];
 #pragma unroll
@@ -378,7 +408,7 @@ __device__ __forceinline__ void fmat_task(const DevJob& Jb, const DelayRec* __re
           float2 zj = z[i];
 #pragma unroll
           for (int j = 0; j < J; ++j) {
-            f32x16 acc = {};
+            f32x16 acc = {}, acc2 = {};
 #pragma unroll
             for (int g = 0; g < KG; ++g) {
               uint4 b;
@@ -394,6 +424,16 @@ __device__ __forceinline__ void fmat_task(const DevJob& Jb, const DelayRec* __re
               const half8* am = reinterpret_cast<const half8*>(lds) + g * 64 + lane;
               acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(am[64 * KG], B, acc, 0, 0, 0);
               acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(am[0], B, acc, 0, 0, 0);
+              if constexpr (RATE) {
+                acc2 = __builtin_amdgcn_mfma_f32_32x32x16_f16(am[192 * KG], B, acc2, 0, 0, 0);
+                acc2 = __builtin_amdgcn_mfma_f32_32x32x16_f16(am[128 * KG], B, acc2, 0, 0, 0);
+              }
+            }
+            if constexpr (RATE) {
+              // sample n - N / 2 = t + T (e - RAD / 2)
+              const float t = (float)(tp + L * j);
+#pragma unroll
+              for (int k = 0; k < 16; ++k) acc[k] = fmaf(t, acc[k], (float)(N / 2) * acc2[k]);
             }
             // P[k] = zj Wj^k
             float2 Wa = W1[i];
@@ -483,21 +523,25 @@ __device__ __forceinline__ void fmat_task(const DevJob& Jb, const DelayRec* __re
             const float2* fdl = fdt + rho / R * K;
             if (fl < nf) {
               // bin kap + R m (low precision: channel-blocked, lp_index)
-              const size_t row = OUT == kOutF32 ? ((size_t)(sb * nf + fl) * M + m_in) * n_chan + kap
+              const size_t row = F32 ? ((size_t)(sb * nf + fl) * M + m_in) * n_chan + kap
                                                 : (size_t)(sb * nf + fl) * M * n_chan +
                                                       (m_in + (kap >> 4) * M) * 16 + (kap & 15);
               uint2 ex[2];
-              if constexpr (OUT != kOutF32) {
+              if constexpr (!F32) {
                 // bin kap + R m: exponent byte m / (N / 16 / R) of the word at its remainder
                 const uint2* exw = reinterpret_cast<const uint2*>(
                     scale_exp + ((size_t)sb * M + m_in) * n_chan);
                 ex[0] = exw[kap];
                 ex[1] = L == 32 ? exw[kap + R] : ex[0];
               }
+              const float rho = RATE ? drec[(size_t)s * nf + fl].rate : 0.f;
 #pragma unroll
               for (int m = 0; m < K; ++m) {
                 const float2 y = cmul(a[m], fdl[m]);
-                if constexpr (OUT == kOutF32) {
+                if constexpr (RATE) {
+                  add_drift(static_cast<float2*>(spec) + row + R * m, y, rho,
+                            (float)(kap + R * m) / (float)N);
+                } else if constexpr (OUT == kOutF32) {
                   put_spec<OUT>(spec, row + R * m, y, 0);
                 } else {
                   const int byte = L == 32 ? m >> 1 : m;
@@ -572,18 +616,19 @@ __device__ __forceinline__ void fmat_task(const DevJob& Jb, const DelayRec* __re
               u[i][a].y = x2[(a * KB + 2 * w + (i & 1) + (KB / 2) * (i >> 1)) * 64];
           __syncthreads();   // the next input writes the rows
           if (f0 < nf) {
-            const size_t row = OUT == kOutF32 ? ((size_t)(sb * nf + f0) * M + m_in) * n_chan + 16 * hh +
+            const size_t row = F32 ? ((size_t)(sb * nf + f0) * M + m_in) * n_chan + 16 * hh +
                                                     RAD * (lane >> 4) + (lane & 15)
                                               : (size_t)(sb * nf + f0) * M * n_chan +
                                                     (m_in + (lane >> 4) * M) * 16 + (lane & 15);
             uint2 ex[2];
-            if constexpr (OUT != kOutF32) {
+            if constexpr (!F32) {
               // bin lane + 64 kr, kr = kb + KB ka: byte kr / (N / 1024) of the word at the remainder
               const uint2* exw =
                   reinterpret_cast<const uint2*>(scale_exp + ((size_t)sb * M + m_in) * n_chan);
 #pragma unroll
               for (int i = 0; i < 2; ++i) ex[i] = exw[lane + 64 * ((2 * w + i) & (N / 1024 - 1))];
             }
+            const float rho = RATE ? drec[(size_t)s * nf + f0].rate : 0.f;
 #pragma unroll
             for (int i = 0; i < NB; ++i) {
               const int kb = 2 * w + (i & 1) + (KB / 2) * (i >> 1);
@@ -594,7 +639,10 @@ __device__ __forceinline__ void fmat_task(const DevJob& Jb, const DelayRec* __re
               for (int a = 0; a < KA / 2; ++a) {
                 const float2 y = cmul(u[i][a], fdt[i * (KA / 2) + a]);
                 const int kr = kb + KB * a;
-                if constexpr (OUT == kOutF32) {
+                if constexpr (RATE) {
+                  add_drift(static_cast<float2*>(spec) + row + R * kr, y, rho,
+                            (float)(lane + R * kr) / (float)N);
+                } else if constexpr (OUT == kOutF32) {
                   put_spec<OUT>(spec, row + R * kr, y, 0);
                 } else {
                   const int byte = kr / (N / 1024);
@@ -612,9 +660,8 @@ __device__ __forceinline__ void fmat_task(const DevJob& Jb, const DelayRec* __re
 }
 
 // The pass-2 twiddles (the first subband's barrier comes before their use).
-template <int N>
+template <class G>
 __device__ __forceinline__ void fmat_tab(unsigned char* lds, const float2* __restrict__ tw) {
-  using G = MGeom<N>;
   if constexpr (G::WPF > 1) {
     float2* tab = reinterpret_cast<float2*>(lds + G::tw_off);
     for (int i = threadIdx.x; i < G::L; i += G::WG)
@@ -625,27 +672,43 @@ __device__ __forceinline__ void fmat_tab(unsigned char* lds, const float2* __res
 // Tasks (station, group of FPG frames, group of ipt inputs), the last
 // fastest; a workgroup takes every n-th.  Tasks cost the same, so they are not
 // fetched from a counter.
+// The drift pass (kOutRate) takes the stations that ask for it, in order.
 template <int N, int OUT>
-__global__ void __attribute__((amdgpu_flat_work_group_size(1, MGeom<N>::WG),
-                               amdgpu_waves_per_eu(MGeom<N>::EU)))
+__global__ void __attribute__((amdgpu_flat_work_group_size(1, MGeom<N, OUT == kOutRate ? 2 : 1>::WG),
+                               amdgpu_waves_per_eu(MGeom<N, OUT == kOutRate ? 2 : 1>::EU)))
     k_fmat(const DevJob* __restrict__ job, const DelayRec* __restrict__ drec,
            const PhaseRec* __restrict__ prec, const float2* __restrict__ tw,
            void* __restrict__ spec, const int8_t* __restrict__ scale_exp, int nf, int ipt) {
-  using G = MGeom<N>;
+  constexpr bool RATE = OUT == kOutRate;
+  using G = MGeom<N, RATE ? 2 : 1>;
   extern __shared__ __attribute__((aligned(16))) unsigned char fmat_lds[];
   const DevJob& J = *job;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int unit = wave / G::WPF;
   float* rows = reinterpret_cast<float*>(fmat_lds + G::rows_off) + unit * G::unit_f;
   float2* fdt = reinterpret_cast<float2*>(fmat_lds + G::fd_off) + wave * G::fd_n;
-  fmat_tab<N>(fmat_lds, tw);
+  fmat_tab<G>(fmat_lds, tw);
   const int n_in = J.n_inputs;
   const int n_ig = (n_in + ipt - 1) / ipt, per_station = (nf + G::FPG - 1) / G::FPG * n_ig;
-  const int n_tasks = per_station * J.n_stations;
+  int n_stations = J.n_stations;
+  if constexpr (RATE) {
+    n_stations = 0;
+    for (int i = 0; i < J.n_stations; ++i) n_stations += J.st[i].rate_correct ? 1 : 0;
+  }
+  const int n_tasks = per_station * n_stations;
 #pragma unroll 1
   for (int task = blockIdx.x; task < n_tasks; task += gridDim.x) {
-    const int s = task / per_station, rem = task - s * per_station;
+    int s = task / per_station;
+    const int rem = task - s * per_station;
     const int grp = rem / n_ig, in = (rem - grp * n_ig) * ipt;
+    if constexpr (RATE) {
+      int k = s;   // the s-th station that asks for it
+      s = -1;
+      do {
+        ++s;
+        k -= J.st[s].rate_correct ? 1 : 0;
+      } while (k >= 0);
+    }
     fmat_task<N, OUT>(J, drec, prec, spec, scale_exp, nf, s, grp * G::FPG,
                       grp * G::FPG + unit * G::FPW, in, min(in + ipt, n_in), wave, wave % G::WPF,
                       fmat_lds, rows, fdt, tw);
@@ -660,7 +723,7 @@ __global__ void __attribute__((amdgpu_flat_work_group_size(1, MGeom<N>::WG),
                  const float2* __restrict__ tw) {
   using G = MGeom<N>;
   extern __shared__ __attribute__((aligned(16))) unsigned char fmat_lds[];
-  fmat_tab<N>(fmat_lds, tw);
+  fmat_tab<G>(fmat_lds, tw);
   const FusedItemsK items = fused_const(items_g);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int unit = wave / G::WPF;
@@ -712,7 +775,7 @@ template <int N, int OUT>
 hipError_t launch_fmat_no(const DevJob* job, int n_stations, int n_subbands, int n_pols,
                           const DelayRec* drec, const PhaseRec* prec, const float2* tw, void* spec,
                           const int8_t* scale_exp, int nf, hipStream_t s) {
-  using G = MGeom<N>;
+  using G = MGeom<N, OUT == kOutRate ? 2 : 1>;
   static std::atomic<int> cache[64];
   int res = 0;
   hipError_t e = resident_groups(k_fmat<N, OUT>, G::WG, G::lds_bytes, cache, res);
@@ -733,6 +796,10 @@ hipError_t launch_fmat_n(const DevJob* job, int n_stations, int n_subbands, int 
     if (out == kOutF16)
       return launch_fmat_no<N, kOutF16>(job, n_stations, n_subbands, n_pols, drec, prec, tw, spec,
                                         scale_exp, nf, s);
+  if constexpr (matrix_rate_ok(N))
+    if (out == kOutRate)
+      return launch_fmat_no<N, kOutRate>(job, n_stations, n_subbands, n_pols, drec, prec, tw, spec,
+                                         nullptr, nf, s);
   if (out != kOutF32) return hipErrorInvalidValue;
   return launch_fmat_no<N, kOutF32>(job, n_stations, n_subbands, n_pols, drec, prec, tw, spec, scale_exp,
                                     nf, s);
@@ -805,6 +872,13 @@ hipError_t launch_fmat(int N, const DevJob* job, int n_stations, int n_subbands,
                                             spec, nullptr, nf, s);
     default: return hipErrorInvalidValue;
   }
+}
+
+hipError_t launch_fmat_rate(int N, const DevJob* job, int n_flagged, int n_subbands, int n_pols,
+                            const DelayRec* drec, const PhaseRec* prec, const float2* tw,
+                            void* spec, int nf, hipStream_t s) {
+  return launch_fmat(N, job, n_flagged, n_subbands, n_pols, drec, prec, tw, spec, nullptr, nf,
+                     kOutRate, s);
 }
 
 hipError_t launch_fmat_fused(int N, const FusedItem* items, int n_items, int n_tasks,

@@ -162,6 +162,15 @@ hipError_t launch_fstage(int N, const DevJob* job, int n_stations, int n_subband
 hipError_t launch_fmat(int N, const DevJob* job, int n_stations, int n_subbands, int n_pols,
                        const DelayRec* drec, const PhaseRec* prec, const float2* tw, void* spec,
                        const int8_t* scale_exp, int nf, int out, hipStream_t s);
+// Frame lengths whose drift correction runs on the matrix cores.  At 4096 points (two
+// waves a frame in groups of four, 179 registers) the vector kernel's pass is faster:
+// 525 against 538 us for k_fmat's job of 5 stations; the other lengths stand there.
+constexpr bool matrix_rate_ok(int N) { return N <= kMaxRateCorrectN && N != 4096; }
+// The drift correction on the matrix cores (matrix_rate_ok), after launch_fmat's
+// FP32 spectra of the same block: n_flagged of the job's stations ask for it.
+hipError_t launch_fmat_rate(int N, const DevJob* job, int n_flagged, int n_subbands, int n_pols,
+                            const DelayRec* drec, const PhaseRec* prec, const float2* tw,
+                            void* spec, int nf, hipStream_t s);
 hipError_t launch_fmat_fused(int N, const FusedItem* items, int n_items, int n_tasks,
                              const float2* tw, hipStream_t s);
 int fmat_inputs_per_task(int N, int n_stations, int n_subbands, int n_pols, int nf);

@@ -346,6 +346,22 @@ int upload_desc(xc_ctx* c, const xc_setup* s, const xc_station* st, const Layout
   return XC_OK;
 }
 
+// The drift correction over a block's FP32 spectra, by the kernel that wrote them.
+static hipError_t launch_rate_pass(const xc_setup* s, const xc_station* st, bool mat, int tuned,
+                                   const DevJob* dj, const DelayRec* drec, const PhaseRec* prec,
+                                   const float2* tw, void* spec, int nf, unsigned* ctr,
+                                   hipStream_t stream) {
+  const int N = 2 * s->n_chan, S = s->n_stations, nsb = s->n_subbands;
+  if (matrix_rate_ok(N) &&
+      fstage_variant(tuned, mat, s->n_pols, s->n_chan, kOutF32, s->n_frames) == kFstageMatrix) {
+    int flagged = 0;
+    for (int i = 0; i < S; ++i) flagged += st[i].rate_correct ? 1 : 0;
+    return launch_fmat_rate(N, dj, flagged, nsb, s->n_pols, drec, prec, tw, spec, nf, stream);
+  }
+  return launch_fstage(N, dj, S, nsb, nsb * s->n_pols, drec, prec, tw, spec, nullptr, nf,
+                       kFstageRatePass, kOutF32, ctr, nullptr, stream);
+}
+
 int slots_used(int nf, int fps_max, int M, int n_chan, int n_subbands) {
   int n = 0, fps = 0;
   xmac_splits(nf, fps_max, M, n_chan, n_subbands, n, fps);
@@ -419,9 +435,8 @@ int enqueue_job(xc_ctx* c, const xc_setup* s, const xc_station* st, const xc_out
     if (e != hipSuccess) return hip_fail(c, e, "fstage");
     if (rate_pass) {
       e = timed(c, XC_K_FSTAGE, stream, [&] {
-        return launch_fstage(N, dj, S, nsb, nsb * s->n_pols, drec_p, prec_p, c->d_tw, spec_p, sexp,
-                             nf, kFstageRatePass, L.out, ctr_p + 1,
-                             reinterpret_cast<float2*>(arena + L.scratch), stream);
+        return launch_rate_pass(s, st, mat, tu.fstage_waves_per_simd, dj, drec_p, prec_p, c->d_tw,
+                                spec_p, nf, ctr_p + 1, stream);
       });
       if (e != hipSuccess) return hip_fail(c, e, "fstage drift correction");
     }
@@ -845,9 +860,8 @@ int xc_debug_spectra(xc_ctx* c, const xc_setup* s, const xc_station* st, int64_t
                       kOutF32, ctr,
                       reinterpret_cast<float2*>(p.arena + p.L.scratch), stream);
   if (e == hipSuccess && any_rate_correct(s, st))
-    e = launch_fstage(2 * s->n_chan, dj, s->n_stations, s->n_subbands,
-                      s->n_subbands * s->n_pols, drec, prec, c->d_tw, spectra, nullptr, n, kFstageRatePass, kOutF32, ctr + 1,
-                      reinterpret_cast<float2*>(p.arena + p.L.scratch), stream);
+    e = launch_rate_pass(s, st, fstage_matrix_ok(s, st), p.tu.fstage_waves_per_simd, dj, drec, prec,
+                         c->d_tw, spectra, n, ctr + 1, stream);
   return e == hipSuccess ? XC_OK : hip_fail(c, e, "debug_spectra");
 }
 
