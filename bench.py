@@ -54,7 +54,7 @@ def kernel_source_hash(files) -> str:
     return h.hexdigest()[:16]
 
 
-F_SOURCES = ["k_fstage.hip", "xc_fft.h", "xc_dev.h"]
+F_SOURCES = ["k_fmat.hip", "k_fstage.hip", "xc_fft.h", "xc_spec.h", "xc_dev.h"]
 X_SOURCES = ["k_xmac.hip", "xc_dev.h"]
 
 
@@ -283,7 +283,7 @@ def _counter_means(db_path: str, counter: str) -> dict:
 # The C2 workload's F and X kernels in a counter database: the F-stage and
 # X-stage kernels of its FFT length and input count, whatever variant the
 # library's defaults pick (the one with the most dispatches).
-C2_KERNELS = {"fstage": (("xc::k_fstage<2048,",), F_SOURCES),
+C2_KERNELS = {"fstage": (("xc::k_fmat<2048,", "xc::k_fstage<2048,"), F_SOURCES),
               "xmac": (("xc::k_xmac_ringm<20,", "xc::k_xmac_ring<20,", "xc::k_xmac_mfma<5,"),
                        X_SOURCES)}
 
