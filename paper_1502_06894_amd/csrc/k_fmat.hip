@@ -43,7 +43,7 @@
 // stations 1332 us a call against 1124.)
 //
 // Bound by vector issue, at the clock that the chip holds (1.75-1.9 GHz here,
-// 1.93-2.0 in the vector kernel): 38 VALU instructions per station-sample at
+// 1.93-2.0 in the vector kernel): 39 VALU instructions per station-sample at
 // N = 2048 (vector kernel: 44 dual-pol, 58 single-pol), LDS cycles 0.36x.
 // Whole calls of 8 x 4 inputs, 2^24 samples each: N = 512 dual-pol 1.48 ->
 // 1.03 ms, 2048 1.29 -> 1.05, 8192 1.50 -> 1.24, 16384 1.69 -> 1.23,

@@ -57,7 +57,8 @@ struct xc_ctx {
   size_t prof_used = 0;
   float2* d_tw = nullptr;                    // FFT twiddles, kTwiddleN entries
   int scratch_rc = 0;                        // lookup of the allocation-free scratch (hipError_t)
-  unsigned char* h_stage = nullptr;          // kSlots x kSlotBytes pinned, then one word per slot:
+  unsigned char* h_stage = nullptr;          // kSlots x kSlotBytes pinned, then a word per slot
+                                             // (and one that captured calls store to):
   unsigned long long slot_seq[xc::kSlots] = {};   // the upload that last used the slot is done
                                              // when the slot's word says slot_seq
   int next_slot = 0;

@@ -326,23 +326,30 @@ int upload_desc(xc_ctx* c, const xc_setup* s, const xc_station* st, const Layout
                 unsigned char* dev_desc, hipStream_t stream) {
   const size_t arena_off = align_up(L.desc_bytes), bytes = arena_off + L.wst_bytes;
   if (bytes > kSlotBytes) return fail(c, XC_E_INVAL, "descriptor too large");
+  // A call that is being captured uploads only when its graph runs, if ever: its
+  // slot stays free, and its replays store to a word that nobody waits for (as a
+  // recorded slot the next turn of the ring would wait for the graph).
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  hipError_t e = stream ? hipStreamIsCapturing(stream, &cap) : hipSuccess;
+  if (e != hipSuccess) return hip_fail(c, e, "hipStreamIsCapturing");
+  const bool captured = cap != hipStreamCaptureStatusNone;
   const int k = c->next_slot;
   c->next_slot = (k + 1) % kSlots;
-  hipError_t e = wait_slot(c, k);
+  e = wait_slot(c, k);
   if (e != hipSuccess) return hip_fail(c, e, "descriptor slot");
   unsigned char* h = c->h_stage + (size_t)k * kSlotBytes;
   build_desc(s, st, L, dev_desc, h);
   memset(h + arena_off, 0, L.wst_bytes);
   const unsigned long long seq = c->slot_seq[k] + 1;
   if (reinterpret_cast<uintptr_t>(dev_desc) % 16 == 0) {
-    e = launch_upload(h, dev_desc, bytes, slot_words(c) + k, seq, stream);
+    e = launch_upload(h, dev_desc, bytes, slot_words(c) + (captured ? kSlots : k), seq, stream);
   } else {   // (a workspace that starts on an odd address)
     e = hipMemcpyAsync(dev_desc, h, bytes, hipMemcpyHostToDevice, stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(stream);
-    slot_words(c)[k] = seq;
+    if (e == hipSuccess && !captured) e = hipStreamSynchronize(stream);
+    if (!captured) slot_words(c)[k] = seq;
   }
   if (e != hipSuccess) return hip_fail(c, e, "descriptor upload");
-  c->slot_seq[k] = seq;
+  if (!captured) c->slot_seq[k] = seq;
   return XC_OK;
 }
 
@@ -570,9 +577,9 @@ int xc_create(xc_ctx** out, int hip_device) {
     e = hipMemcpy(c->d_tw, tw.data(), sizeof(float2) * kTwiddleN, hipMemcpyHostToDevice);
   if (e == hipSuccess)
     e = hipHostMalloc((void**)&c->h_stage,
-                      (size_t)kSlots * (kSlotBytes + sizeof(unsigned long long)),
+                      (size_t)kSlots * kSlotBytes + (kSlots + 1) * sizeof(unsigned long long),
                       hipHostMallocDefault);
-  if (e == hipSuccess) memset(slot_words(c), 0, kSlots * sizeof(unsigned long long));
+  if (e == hipSuccess) memset(slot_words(c), 0, (kSlots + 1) * sizeof(unsigned long long));
   if (e == hipSuccess) c->scratch_rc = (int)scratch_lookup(hip_device);
   if (e != hipSuccess) {
     xc_destroy(c);
