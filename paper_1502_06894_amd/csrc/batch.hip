@@ -131,6 +131,9 @@ uint64_t batch_key(const xc_job* jobs, int n, int lanes, const Plan& P, const vo
       h = fnv(h, &st.n_frames_m5b, 2 * sizeof(int64_t));
       h = fnv(h, &st.frame_ok, sizeof st.frame_ok);
       h = fnv(h, &st.poly_deg, sizeof st.poly_deg);
+      // the drift pass: its launches, and whether the job is fused at all
+      const int32_t flags[2] = {st.rate_correct != 0, st.phase_poly != nullptr};
+      h = fnv(h, flags, sizeof flags);
       h = fnv(h, st.delay_poly, sizeof(double) * (st.poly_deg + 1));
       if (st.phase_poly)
         h = fnv(h, st.phase_poly, sizeof(double) * s.n_subbands * (st.poly_deg + 1));
