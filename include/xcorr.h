@@ -167,7 +167,10 @@ int xc_correlate_subint(xc_ctx* ctx, const xc_setup* setup, const xc_station* st
  * scratch: calls in order on one stream are safe, calls that overlap on one
  * GPU (other streams, other threads, other contexts) race.  Results equal
  * xc_correlate_subint's at the same frames per block.  Async on `stream`.
- * Errors as for xc_correlate_subint. */
+ * Errors as for xc_correlate_subint.  A captured call (this one or
+ * xc_correlate_subint) records the job description with its launches: the graph
+ * may be replayed any number of times, whatever else the context runs, while
+ * the context, recordings, outputs and workspace stay. */
 int xc_correlate_subint_noalloc(xc_ctx* ctx, const xc_setup* setup, const xc_station* st,
                                 const xc_output* out, void* stream);
 size_t xc_noalloc_scratch_bytes(void);

@@ -1,5 +1,7 @@
 // Small kernels: recording ingest (A0), delay/phase model per frame and
 // station-pair weights (A1), weight clearing, finalise (A8) and the unpack test tap.
+#include <string.h>
+
 #include "xc_launch.h"
 
 namespace xc {
@@ -33,24 +35,52 @@ hipError_t launch_zero(unsigned long long* p, size_t n, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Copy n 16-byte words from pinned host memory (a descriptor: a few KB) to the
-// device, then tell the host by writing seq to *done, also pinned.  One
-// workgroup, and no event: a copy command, or an event behind the kernel, keeps
-// the stream's next kernel waiting some 5 us, a sixth of a short call.
-__global__ void __launch_bounds__(1024)
-    k_upload(const uint4* src, uint4* __restrict__ dst, int n, unsigned long long* done,
-             unsigned long long seq) {
-  for (int i = threadIdx.x; i < n; i += 1024) dst[i] = src[i];
-  __syncthreads();
-  if (threadIdx.x == 0)
-    __hip_atomic_store(done, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+// Write n words of a descriptor, which come in the launch's own arguments, and
+// clear nw weights.  No staging buffer lies between the call and its launch, so
+// nothing is waited for or reused, and a graph that records the launch records
+// the descriptor with it.  A chunk and the other arguments stay below 4 KB; most
+// descriptors are one or two chunks.
+template <int W>
+struct DescChunk {
+  uint32_t w[W];
+};
+
+template <int W>
+__global__ void __launch_bounds__(W)
+    k_desc(const DescChunk<W> c, uint32_t* __restrict__ dst, int n,
+           unsigned long long* __restrict__ wst, int nw) {
+  const int i = threadIdx.x;
+  if (i < n) dst[i] = c.w[i];
+  for (int k = i; k < nw; k += W) wst[k] = 0;
 }
 
-hipError_t launch_upload(const void* host, void* dst, size_t bytes, unsigned long long* done,
-                         unsigned long long seq, hipStream_t s) {
-  hipLaunchKernelGGL(k_upload, dim3(1), dim3(1024), 0, s, static_cast<const uint4*>(host),
-                     static_cast<uint4*>(dst), (int)(bytes / 16), done, seq);
+template <int W>
+static hipError_t launch_desc_chunk(const uint32_t* src, uint32_t* dst, int n,
+                                    unsigned long long* wst, int nw, hipStream_t s) {
+  DescChunk<W> c;
+  memcpy(c.w, src, n * sizeof(uint32_t));
+  hipLaunchKernelGGL(k_desc<W>, dim3(1), dim3(W), 0, s, c, dst, n, wst, nw);
   return hipGetLastError();
+}
+
+hipError_t launch_desc(const void* host, void* dst, size_t bytes, unsigned long long* wst, int nw,
+                       hipStream_t s) {
+  // the host copies the arguments twice, so calls of up to three stations (whose
+  // time is the host's) pass 768 bytes: 32.5 us a call, 32.7 with 1 KB (32.9 with a
+  // pinned buffer, which has to be kept and waited for)
+  constexpr int kSmall = 192, kLarge = 896;
+  const uint32_t* h = static_cast<const uint32_t*>(host);
+  uint32_t* d = static_cast<uint32_t*>(dst);
+  hipError_t e = hipSuccess;
+  for (int n = (int)(bytes / sizeof(uint32_t)); n > 0 && e == hipSuccess; nw = 0) {
+    const int k = n < kLarge ? n : kLarge;
+    e = k <= kSmall ? launch_desc_chunk<kSmall>(h, d, k, wst, nw, s)
+                    : launch_desc_chunk<kLarge>(h, d, k, wst, nw, s);
+    h += k;
+    d += k;
+    n -= k;
+  }
+  return e;
 }
 
 // Delay record (subband 0 only) and phase record of frame fl of a block

@@ -60,10 +60,11 @@ __device__ inline FusedItemsK fused_const(const FusedItem* items) { return (Fuse
 // A0: frame_ok[f] = sync word of recording frame f is good.
 hipError_t launch_ingest(const uint32_t* words, int64_t n_frames, uint8_t* frame_ok,
                          hipStream_t s);
-// Copy `bytes` (a multiple of 16) of pinned host memory to 16-byte aligned
-// device memory, then set the pinned word *done to seq.
-hipError_t launch_upload(const void* host, void* dst, size_t bytes, unsigned long long* done,
-                         unsigned long long seq, hipStream_t s);
+// Write `bytes` (a multiple of 4) of host memory to dst and clear nw words at wst.
+// The bytes travel in the launches' arguments: they are read before this returns,
+// and a capture records them.
+hipError_t launch_desc(const void* host, void* dst, size_t bytes, unsigned long long* wst, int nw,
+                       hipStream_t s);
 // Zero n 64-bit words.
 hipError_t launch_zero(unsigned long long* p, size_t n, hipStream_t s);
 // A1: delay and phase records for frames f0 .. f0+nf-1 of every station; also

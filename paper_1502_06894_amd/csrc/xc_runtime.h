@@ -18,8 +18,6 @@
 
 namespace xc {
 
-constexpr int kSlots = 8;                 // pinned descriptor staging slots per context
-constexpr size_t kSlotBytes = 256 * 1024;
 constexpr size_t kAlign = 256;
 constexpr int kMaxBlockFrames = 65536;
 // Default frames per block: 2048, or more while the block's staged spectra
@@ -57,11 +55,7 @@ struct xc_ctx {
   size_t prof_used = 0;
   float2* d_tw = nullptr;                    // FFT twiddles, kTwiddleN entries
   int scratch_rc = 0;                        // lookup of the allocation-free scratch (hipError_t)
-  unsigned char* h_stage = nullptr;          // kSlots x kSlotBytes pinned, then a word per slot
-                                             // (and one that captured calls store to):
-  unsigned long long slot_seq[xc::kSlots] = {};   // the upload that last used the slot is done
-                                             // when the slot's word says slot_seq
-  int next_slot = 0;
+  std::vector<unsigned char> desc;           // descriptor being built (single jobs)
   std::vector<hipStream_t> lanes;            // batch lanes (default priority)
   std::vector<hipEvent_t> lane_ev;           // join events, one per lane
   hipEvent_t fork_ev = nullptr;
@@ -133,9 +127,8 @@ int shared_block_frames(const xc_setup& s, const Layout& L, size_t cap_bytes, in
 // Descriptor for device address `dev_desc`.
 void build_desc(const xc_setup* s, const xc_station* st, const Layout& L,
                 const unsigned char* dev_desc, unsigned char* h);
-// Stage one descriptor, and zeros for the arena's weights that follow it,
-// through a pinned ring slot and copy them to dev_desc (the arena starts
-// align_up(L.desc_bytes) after it).
+// Build one descriptor and write it to dev_desc; clear the weights of the arena,
+// which starts align_up(L.desc_bytes) after it.
 int upload_desc(xc_ctx* c, const xc_setup* s, const xc_station* st, const Layout& L,
                 unsigned char* dev_desc, hipStream_t stream);
 // Does any station ask for the drift correction inside frames?

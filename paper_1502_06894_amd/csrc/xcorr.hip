@@ -4,9 +4,7 @@
 
 #include <algorithm>
 #include <atomic>
-#include <chrono>
 #include <mutex>
-#include <thread>
 
 #include "xc_runtime.h"
 
@@ -301,56 +299,19 @@ void build_desc(const xc_setup* s, const xc_station* st, const Layout& L,
   }
 }
 
-static unsigned long long* slot_words(xc_ctx* c) {
-  return reinterpret_cast<unsigned long long*>(c->h_stage + (size_t)kSlots * kSlotBytes);
-}
-
-// Wait until the slot's last upload has read it (seldom: kSlots calls ahead of
-// the device): look a few thousand times, then every 20 us.  After 10 s without
-// it the device is asked for everything it still has, which reports an error
-// that would keep the word from changing.
-static hipError_t wait_slot(xc_ctx* c, int k) {
-  const unsigned long long* w = slot_words(c) + k;
-  auto done = [&] { return __atomic_load_n(w, __ATOMIC_ACQUIRE) == c->slot_seq[k]; };
-  for (int i = 0; i < 4096; ++i)
-    if (done()) return hipSuccess;
-  for (int i = 0; i < 500000; ++i) {
-    if (done()) return hipSuccess;
-    std::this_thread::sleep_for(std::chrono::microseconds(20));
-  }
-  const hipError_t e = hipDeviceSynchronize();
-  return e != hipSuccess ? e : done() ? hipSuccess : hipErrorUnknown;
-}
-
 int upload_desc(xc_ctx* c, const xc_setup* s, const xc_station* st, const Layout& L,
                 unsigned char* dev_desc, hipStream_t stream) {
-  const size_t arena_off = align_up(L.desc_bytes), bytes = arena_off + L.wst_bytes;
-  if (bytes > kSlotBytes) return fail(c, XC_E_INVAL, "descriptor too large");
-  // A call that is being captured uploads only when its graph runs, if ever: its
-  // slot stays free, and its replays store to a word that nobody waits for (as a
-  // recorded slot the next turn of the ring would wait for the graph).
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  hipError_t e = stream ? hipStreamIsCapturing(stream, &cap) : hipSuccess;
-  if (e != hipSuccess) return hip_fail(c, e, "hipStreamIsCapturing");
-  const bool captured = cap != hipStreamCaptureStatusNone;
-  const int k = c->next_slot;
-  c->next_slot = (k + 1) % kSlots;
-  e = wait_slot(c, k);
-  if (e != hipSuccess) return hip_fail(c, e, "descriptor slot");
-  unsigned char* h = c->h_stage + (size_t)k * kSlotBytes;
-  build_desc(s, st, L, dev_desc, h);
-  memset(h + arena_off, 0, L.wst_bytes);
-  const unsigned long long seq = c->slot_seq[k] + 1;
-  if (reinterpret_cast<uintptr_t>(dev_desc) % 16 == 0) {
-    e = launch_upload(h, dev_desc, bytes, slot_words(c) + (captured ? kSlots : k), seq, stream);
-  } else {   // (a workspace that starts on an odd address)
-    e = hipMemcpyAsync(dev_desc, h, bytes, hipMemcpyHostToDevice, stream);
-    if (e == hipSuccess && !captured) e = hipStreamSynchronize(stream);
-    if (!captured) slot_words(c)[k] = seq;
-  }
-  if (e != hipSuccess) return hip_fail(c, e, "descriptor upload");
-  if (!captured) c->slot_seq[k] = seq;
-  return XC_OK;
+  c->desc.resize(L.desc_bytes);
+  build_desc(s, st, L, dev_desc, c->desc.data());
+  // (the phase polynomials come last, and are read only where a station has them)
+  size_t bytes = sizeof(DevJob) + (size_t)s->n_stations * sizeof(DevStation);
+  for (int i = 0; i < s->n_stations; ++i)
+    if (st[i].phase_poly) bytes = L.desc_bytes;
+  unsigned long long* wst =
+      reinterpret_cast<unsigned long long*>(dev_desc + align_up(L.desc_bytes) + L.wst);
+  const hipError_t e = launch_desc(c->desc.data(), dev_desc, bytes, wst,
+                                   (int)(L.wst_bytes / sizeof(unsigned long long)), stream);
+  return e == hipSuccess ? XC_OK : hip_fail(c, e, "descriptor upload");
 }
 
 // The drift correction over a block's FP32 spectra, by the kernel that wrote them.
@@ -575,11 +536,6 @@ int xc_create(xc_ctx** out, int hip_device) {
   }
   if (e == hipSuccess)
     e = hipMemcpy(c->d_tw, tw.data(), sizeof(float2) * kTwiddleN, hipMemcpyHostToDevice);
-  if (e == hipSuccess)
-    e = hipHostMalloc((void**)&c->h_stage,
-                      (size_t)kSlots * kSlotBytes + (kSlots + 1) * sizeof(unsigned long long),
-                      hipHostMallocDefault);
-  if (e == hipSuccess) memset(slot_words(c), 0, (kSlots + 1) * sizeof(unsigned long long));
   if (e == hipSuccess) c->scratch_rc = (int)scratch_lookup(hip_device);
   if (e != hipSuccess) {
     xc_destroy(c);
@@ -597,8 +553,6 @@ void xc_destroy(xc_ctx* c) {
     (void)hipEventDestroy(t.a);
     (void)hipEventDestroy(t.b);
   }
-  if (c->h_stage)
-    for (int k = 0; k < kSlots; ++k) (void)wait_slot(c, k);
   for (auto& g : c->graphs) hipGraphExecDestroy(g.exec);
   for (size_t i = 0; i < c->lanes.size(); ++i) {
     (void)hipStreamSynchronize(c->lanes[i]);
@@ -619,7 +573,6 @@ void xc_destroy(xc_ctx* c) {
     (void)hipEventDestroy(c->batch_ev);
   }
   if (c->h_batch) (void)hipHostFree(c->h_batch);
-  if (c->h_stage) (void)hipHostFree(c->h_stage);
   if (c->d_tw) (void)hipFree(c->d_tw);
   delete c;
 }
