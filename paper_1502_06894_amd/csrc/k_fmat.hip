@@ -670,8 +670,15 @@ __device__ __forceinline__ void fmat_tab(unsigned char* lds, const float2* __res
 }
 
 // Tasks (station, group of FPG frames, group of ipt inputs), the last
-// fastest; a workgroup takes every n-th.  Tasks cost the same, so they are not
-// fetched from a counter.
+// fastest; a workgroup takes every n-th.  Tasks of full input groups cost the
+// same, so they are not fetched from a counter.  Where the number of groups
+// divides that of the workgroups, a workgroup would meet the same group of inputs
+// in every round, and with a smaller last group (five or six inputs: 4 + 1, 4 + 2)
+// half of the workgroups would wait for the others; so the groups turn by one
+// each round.  (A frame group's tasks lie in one round then.)  Whole calls, before ->
+// with it: 7 stations of 6 inputs, 2^25 samples each, N = 4096 3757 -> 3167 us,
+// 16384 4119 -> 3494; 8 stations of 5 inputs, 2^26, N = 2048 5873 -> 5403, 4096
+// 6799 -> 6079 (the vector kernel's 6166); equal groups +-0.7 %.
 // The drift pass (kOutRate) takes the stations that ask for it, in order.
 template <int N, int OUT>
 __global__ void __attribute__((amdgpu_flat_work_group_size(1, MGeom<N, OUT == kOutRate ? 2 : 1>::WG),
@@ -696,11 +703,17 @@ __global__ void __attribute__((amdgpu_flat_work_group_size(1, MGeom<N, OUT == kO
     for (int i = 0; i < J.n_stations; ++i) n_stations += J.st[i].rate_correct ? 1 : 0;
   }
   const int n_tasks = per_station * n_stations;
+  const bool turn = gridDim.x % n_ig == 0;
+  int shift = 0;
 #pragma unroll 1
   for (int task = blockIdx.x; task < n_tasks; task += gridDim.x) {
     int s = task / per_station;
     const int rem = task - s * per_station;
-    const int grp = rem / n_ig, in = (rem - grp * n_ig) * ipt;
+    const int grp = rem / n_ig;
+    int ig = rem - grp * n_ig + shift;
+    if (ig >= n_ig) ig -= n_ig;
+    const int in = ig * ipt;
+    if (turn && ++shift == n_ig) shift = 0;
     if constexpr (RATE) {
       int k = s;   // the s-th station that asks for it
       s = -1;
