@@ -41,3 +41,23 @@ def test_every_spectrum(n_chan, C, S, nsb, P, nf):
         assert torch.isfinite(d).all() and n.min().item() > 0.0
         worst = max(worst, (d / n).max().item())
     assert 0.0 < worst < 5e-6, worst
+
+
+def test_fused_batch_rounds():
+    """The same over the fused batch's tasks, which go over all jobs of a length: the
+    bits of each job alone."""
+    from paper_1502_06894_amd import xcorr as xc
+    corr = xc.Correlator(0)
+    jobs = []
+    for k, (n_chan, S, nsb, P, nf) in enumerate([
+            (256, 5, 3, 2, 2501), (256, 3, 5, 1, 3000), (2048, 4, 3, 2, 401), (2048, 5, 7, 1, 203),
+            (2048, 3, 1, 1, 300), (8192, 3, 5, 1, 99), (8192, 2, 5, 2, 101)]):
+        jobs.append(configs.small_job("cuda", n_stations=S, n_subbands=nsb, n_pols=P,
+                                      n_chan=n_chan, C=16, n_frames=nf, seed=k))
+    ws = corr.batch_workspace(jobs, n_lanes=2)
+    ws.fill_(255)
+    got = corr.correlate_batch(jobs, n_lanes=2, workspace=ws)
+    torch.cuda.synchronize()
+    for k, (j, (v, w)) in enumerate(zip(jobs, got)):
+        rv, rw = corr.correlate(j)
+        assert torch.equal(v, rv) and torch.equal(w, rw), k
