@@ -188,11 +188,14 @@ bool fstage_matrix_ok(const xc_setup* s, const xc_station* st) {
     }
   }
   // left out of the phase, in turns: within a frame 2 phi2 (t - T/2) T (e - 8) <=
-  // N^2 phi2 / 32 and N^2 phi2 / 800 from the step of j; between the F frames
-  // of a task, which share their middle's slope, 9/16 (F - 1) N^2 phi2; at
-  // 32768 points (radix 32, T = N / 32) half of the first, N^2 phi2 / 64
+  // N^2 phi2 / 32 (half of it at 32768 points, radix 32, T = N / 32); from the step
+  // of j, which takes 4 j L^2 phi2 for (2 t' + j L) j L phi2, 4 L^2 phi2 = N^2 phi2 /
+  // 1024 where a lane has four columns, 3 L^2 phi2 = N^2 phi2 / 341 at 1024 points,
+  // where it has two; between the F frames of a task, which share their middle's
+  // slope, 9/16 (F - 1) N^2 phi2
   const int F = fmat_frames_per_task(N);
-  return phi2 * (double)N * (double)N * ((N == 32768 ? 0.016 : 0.0325) + 0.5625 * (F - 1)) <= 3e-8;
+  const double frame = N == 32768 ? 0.016 : N == 1024 ? 0.0342 : 0.0325;
+  return phi2 * (double)N * (double)N * (frame + 0.5625 * (F - 1)) <= 3e-8;
 }
 
 Layout layout_of(const xc_setup* s, const xc_station* st, const xc_tuning& tu, bool overlap) {
