@@ -1047,8 +1047,8 @@ def main():
     log(f"workload ready in {time.perf_counter() - t:.1f} s: {job.station_samples:.3e} "
         f"station-samples per step")
     corr = _correlator(a)
-    # every step runs the whole path, A0 included: the library checks each
-    # recording frame's sync word (xc_ingest's kernel) inside the call
+    # every step runs the whole path, A0 included: the library checks the sync
+    # words of each window's recording frames inside the call
     ws = corr.alloc_workspace(job, frames_per_block=a.frames_per_block)
     out = corr.alloc_output(job)
     stream = torch.cuda.current_stream()
@@ -1066,7 +1066,7 @@ def main():
           for _ in range(a.steps)]
     T = a.frames_per_block or _default_fpb(job)
     blocks = -(-job.n_frames // T)
-    # per block: delays, F (+ drift pass), X; per call: ingest per station, zero, finalise
+    # per block: delays, F (+ drift pass), X; per call: finalise (with room to spare)
     corr.profile_begin(max_launches=a.steps * (4 * blocks + job.n_stations + 4) + 16)
     torch.cuda.synchronize()
     t0 = time.perf_counter()

@@ -200,13 +200,20 @@ int xc_debug_spectra(xc_ctx* ctx, const xc_setup* setup, const xc_station* st,
 /* Launch-shape parameters of the context (0 = library default / autotuned).
  * They change speed only: results are identical for every setting except
  * frames_per_block, which changes FP32 summation order, and F-stage variants 5
- * and 7, which at FFT lengths of 2048 and below round the last-pass twiddles
- * differently (results stay within the FP32 path's tolerance). */
+ * and 7, which select the vector kernel where the default is the matrix-core one
+ * (other roundings at every FFT length) and, on the vector kernel, round the
+ * last-pass twiddles differently at FFT lengths of 2048 and below (results stay
+ * within the tolerance of the path's precision). */
 typedef struct {
-  int32_t fstage_waves_per_simd;   /* F-stage variant: 0 = default (FP32 spectra: 2 for
-                                      dual-pol jobs with FFT lengths up to 4096, 7 for
-                                      single-pol ones from 1024 to 4096; 7 for FFT lengths
-                                      of 8192 and more; else 1); 1 = one task per station and
+  int32_t fstage_waves_per_simd;   /* F-stage variant: 0 = default: the matrix-core kernel
+                                      for jobs whose fringe phase is close enough to
+                                      linear inside a frame, FP32 at every FFT length,
+                                      FP16 from 512 to 16384 points and 1024 frames; 1-4
+                                      and 8 have no effect on those jobs.  For the others
+                                      the vector kernel (FP32 spectra: 2 for dual-pol jobs
+                                      with FFT lengths up to 4096, 7 for single-pol ones
+                                      from 1024 to 4096; 7 for FFT lengths of 8192 and
+                                      16384; else 1): 1 = one task per station and
                                       frame group, the next task's window words loaded
                                       during the transforms; 2 = the pols of a subband
                                       share their fringe phasors (fewer operations, more
@@ -223,11 +230,8 @@ typedef struct {
                                       1, with the pols of a subband sharing their fringe
                                       phasors, no word prefetch and the fractional-delay
                                       phasors stepped at the store (bit-identical to 1).
-                                      2-4 and 8 apply to FP32 spectra only.  FP32
-                                      jobs, and FP16 ones of 1024 frames and more,
-                                      of FFT length up to 16384 whose fringe phase
-                                      is close enough to linear inside a frame run
-                                      the matrix-core F stage for 0-4 and 8. */
+                                      2-4 and 8 apply to FP32 spectra only; at 32768
+                                      points every vector variant is the same. */
   int32_t xmac_frames_per_stage;   /* X-stage input staging: 8 = ring of 8 one-frame LDS
                                       stages filled by direct memory-to-LDS loads, products
                                       on the vector units (64-channel tiles, at most 32

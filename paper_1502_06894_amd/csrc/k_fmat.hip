@@ -50,6 +50,12 @@
 // 32768 2.00 -> 1.32; the ten-station
 // 4 s scan (N = 2048): F 28.5 -> 26.6 ms.  Its spectra are 2-4e-7 of their RMS
 // from the oracle's (vector kernel: 0.5-2e-6).
+// The gain shrinks where the vector kernel loads a station's words once for more
+// than four inputs.  Whole calls against the vector kernel's, 2^24 to 2^26 samples
+// an input: N = 256 0.94-1.01 up to four inputs a station, 0.98-1.06 single-pol and
+// 1.01-1.10 dual-pol above; 4096 0.95-1.02, dual-pol above eight inputs 1.03-1.04;
+// other lengths 0.70-0.96.  It stays the default there for its accuracy: visibilities
+// 1.6e-7 from 64 bits at N = 256 (vector 1.3e-6), 4.0e-7 at 4096 (1.0e-6).
 #include <atomic>
 
 #include "xc_fft.h"
@@ -100,8 +106,8 @@ struct MGeom {
   static constexpr size_t tw_off = fd_off + (size_t)WAVES * fd_n * sizeof(float2);
   static constexpr size_t lds_bytes = tw_off + (WPF > 1 ? (size_t)L * sizeof(float2) : 0);
   // waves per SIMD asked of the compiler: four (128 registers) leave the short transforms,
-  // with several frames a lane, spilling: F stage of 256-point jobs 0.86 of the vector
-  // kernel's time at two, 1.0 at four; 2048 and 16384 points 0.95 and 0.91 at two, 0.94 and 0.77 at four
+  // with several frames a lane, spilling: 256-point jobs 1.16 of their F stage's time
+  // at two; 2048 and 16384 points 0.99 and 0.85
   // (the drift pass, with twice the accumulators: two at every length; asked for three
   // it spills, 256- and 512-point drift jobs 1.07 and 1.12 of their time, 16384 1.10)
   static constexpr int EU = N <= 1024 || MATS > 1 ? 2 : 4;
@@ -121,9 +127,12 @@ __device__ inline void wave_sync() {
 // The levels as signs: with x, y = +-1 for the upper and lower code bit (offset
 // binary 0 .. 3) the level is 2.16795 x + 1.16795 y (3.3359 = their sum, 1 their
 // difference), so q A is a product of FP16 signs, exact, with two multiples of
-// A, each split into two FP16 terms (22 bits; the split's error is below an FP32
-// rounding's).  kScaleA keeps the lower terms out of FP16's subnormals; a set
-// bit becomes a negative sign, hence the minus.
+// A, each split into two FP16 terms.  Of the product's 24 bits a quarter of the
+// entries lose the last one: 4.8e-8 of the entries' RMS, where one FP32 rounding is
+// 2.8e-8.  (A third term would hold the bit for half as many MFMAs again; with this
+// pass's fewer rounded steps the spectra are closer to 64 bits than the vector
+// kernel's all the same, see the top.)  kScaleA keeps the lower terms out of FP16's
+// subnormals; a set bit becomes a negative sign, hence the minus.
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef _Float16 half2 __attribute__((ext_vector_type(2)));
 typedef _Float16 half4 __attribute__((ext_vector_type(4)));
@@ -134,7 +143,7 @@ __device__ inline uint32_t code_signs(uint32_t x, uint32_t one) {   // both halv
   return (x & 0x80008000u) | one;
 }
 
-// x = hi + lo to about 22 bits.  The product and the upper term are each made
+// x = hi + lo, or one bit less than x.  The product and the upper term are each made
 // once: fused into the conversion, the product would round to another upper
 // term than the one subtracted, an FP16 ulp off, for some of the values.
 __device__ inline half2 split_f16(float x) {
@@ -850,9 +859,11 @@ static_assert(MGeom<256>::FPG == 32 && MGeom<2048>::FPG == 4 && MGeom<4096>::FPG
 int fmat_inputs_per_task(int N, int n_stations, int n_subbands, int n_pols, int nf) {
   // A task's words and phasors are set up once for its inputs, at about 0.3 of an
   // input's time (32 stations x 4 inputs of 8192 points: 7.0 ms at four inputs a
-  // task, 8.5 at one); few tasks leave the last round of the 1024 resident
-  // workgroups half empty.  The split of the subbands (down to single pols where
-  // all tasks fit one round) that takes the least time, the fewest tasks on a tie.
+  // task, 8.5 at one); few tasks leave the last round of the resident workgroups
+  // half empty.  The split of the subbands (down to single pols where all tasks fit
+  // one round) that takes the least time, the fewest tasks on a tie.  Planned with
+  // 1024 workgroups, the number from 2048 to 8192 points (four waves per SIMD); up to
+  // 1024 points 768 are resident, and 512 of eight waves from 16384.
   const int F = fmat_frames_per_task(N);
   const long base = (long)n_stations * ((nf + F - 1) / F);
   int best = 1;

@@ -123,8 +123,9 @@ constexpr int kLeanGroup = 4;   // inputs per lean task
 constexpr int kFstageMatrix = 9;
 constexpr int kMaxMatrixN = 32768;
 // The F-stage variant a job runs.  `mat` (the job passes fstage_matrix_ok, and
-// low-precision spectra matrix_out_ok): the matrix-core kernel, except where
-// variant 5 or 7 is tuned, which round their own way.
+// low-precision spectra matrix_out_ok): the matrix-core kernel, also where one of
+// variants 1-4 and 8 is tuned (settings other than 5 and 7 give the default's results
+// bit for bit, and the kernels round differently); 5 and 7 are the vector kernel's.
 // Otherwise the tuned one, else for FP32 spectra up to
 // N = kShareMaxN variant 2 for dual-pol jobs (pols share their fringe phasors,
 // with the word prefetch and held fractional-delay phasors) and lean tasks
@@ -134,8 +135,8 @@ constexpr int kMaxMatrixN = 32768;
 // single-pol N = 1024 / 2048 / 4096 -7 / -9 / -3 %.
 // Low-precision spectra: the kernels round differently in FP32, so a few
 // spectra land on the neighbouring FP16 or e4m3 value (2e-3 of the FP16 ones).
-// Over 1024 frames of FP16 that averages to below 5e-6 of the products; e4m3's
-// coarser steps would need some 16 000 and keep the vector kernel, as does
+// Over 1024 frames of FP16 that averages to below 5e-6 of the products (1.1-2.4e-6
+// over all lengths); e4m3's coarser steps would need some 16 000 and keep the vector kernel, as does
 // FP16 at 256 points, where its 16-channel runs leave the matrix kernel 3 % behind
 // (32768 points: FP32 only).
 inline bool matrix_out_ok(int N, int out, int64_t n_frames) {
@@ -218,7 +219,7 @@ hipError_t launch_xmac(const DevJob* job, int M, int n_chan, int n_subbands,
 hipError_t launch_finalise(const double2* vacc, int n_slots, size_t slot_stride,
                            const unsigned long long* wst, int n_stations, int n_pols, float2* vis,
                            float* weight, int n_subbands, int M, int n_chan, hipStream_t s);
-// Fused batches (FP32 spectra, the regular F-stage variants 0, kFstageLean and
+// Fused batches (FP32 spectra, F-stage variants kFstageMatrix, 0, kFstageLean and
 // kFstageShare; no drift-correction pass).  `items` is a device table of
 // n_items FusedItem; ctr a zeroed counter (launch_delays_fused clears it).
 // Delay and phase records and station-pair weights of every item's block (+ clears
