@@ -311,7 +311,8 @@ def _dispatch_counts(db_path: str, counter: str) -> dict:
 
 def valu_json(db: str, ss_per_launch: float, kernels: dict) -> dict:
     """VALU instructions per station-sample (SQ_INSTS_VALU x 64 / ss), VALU
-    busy (SQ_ACTIVE_INST_VALU / (256 CUs x GRBM_GUI_ACTIVE / 8 XCDs)) and, where
+    busy (SQ_ACTIVE_INST_VALU / (256 CUs x GRBM_GUI_ACTIVE / 8 XCDs), at most 1:
+    a SIMD can have two instructions in execution, which counts twice) and, where
     the run also counted SQ_VALU_MFMA_BUSY_CYCLES, matrix-core busy per kernel kind."""
     insts = _counter_means(db, "SQ_INSTS_VALU")
     active = _counter_means(db, "SQ_ACTIVE_INST_VALU")
@@ -322,7 +323,7 @@ def valu_json(db: str, ss_per_launch: float, kernels: dict) -> dict:
     for kind, (name, srcs) in kernels.items():
         out[kind] = {"kernel": name, "source_hash": kernel_source_hash(srcs),
                      "instr_per_station_sample": insts[name] * 64.0 / ss_per_launch,
-                     "valu_busy": active[name] / (256.0 * grbm[name] / 8.0)}
+                     "valu_busy": min(1.0, active[name] / (256.0 * grbm[name] / 8.0))}
         if name in mfma:
             # matrix-core busy cycles over 1024 SIMDs x the cycles of one XCD
             out[kind]["mfma_busy"] = mfma[name] / (1024.0 * grbm[name] / 8.0)
